@@ -22,6 +22,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct ArenaLayout {
   size_t tables, rows, magic, pairs, w1, b1, w2, b2, w1t, w2t, w1p, w2p, w1f, w2f;
   std::vector<size_t> w, b;
+  std::vector<size_t> wf;   // fragment-major copies of the row-tile network's layers (net_first)
   size_t total;
 };
 
@@ -109,6 +110,21 @@ bool compact_input(const cold_model &m) {
          dense_grouped_supported(m.dtype, m.widths[1], kept_groups(m) * m.d);
 }
 
+// First layer of the part of the network that the row-tile kernel can run
+// (large batches), or -1: the model's first plain dense layer or a later one.
+int net_first(const cold_model &m) {
+  const int L = m.desc.n_layers;
+  for (int l = compact_input(m) ? 1 : 0; l < L; ++l)
+    if (net_rows_shape(m.dtype, m.widths.data() + l, L - l)) return l;
+  return -1;
+}
+
+// its separate layers (before the two of the tail and the head)
+int net_layers(const cold_model &m) {
+  const int l0 = net_first(m);
+  return l0 < 0 ? 0 : m.desc.n_layers - l0 - 3;
+}
+
 ArenaLayout arena_layout(const cold_model &m) {
   ArenaLayout a;
   size_t off = 0;
@@ -143,6 +159,9 @@ ArenaLayout arena_layout(const cold_model &m) {
     a.w.push_back(take((size_t)m.es * m.widths[l] * m.widths[l + 1]));
     a.b.push_back(take(sizeof(float) * m.widths[l + 1]));
   }
+  const int l0 = net_first(m);
+  for (int i = 0; i < net_layers(m); ++i)
+    a.wf.push_back(take(frag_bytes(m.widths[l0 + i + 1], m.widths[l0 + i])));
   a.total = off;
   return a;
 }
@@ -431,6 +450,11 @@ int cold_load_weights(cold_model *m, const cold_weights *w, void *arena, size_t 
       hipError_t e = launch_pack_frag(w->mlp_w[l], A + al.w[l], m->widths[l + 1], m->widths[l], s);
       if (e != hipSuccess) return hip_fail(m, e, "cold_load_weights: pack");
     }
+  for (int i = 0; i < net_layers(*m); ++i) {
+    const int l = net_first(*m) + i;
+    hipError_t e = launch_pack_frag(w->mlp_w[l], A + al.wf[i], m->widths[l + 1], m->widths[l], s);
+    if (e != hipSuccess) return hip_fail(m, e, "cold_load_weights: pack");
+  }
   hipError_t e = hipStreamSynchronize(s);  // host staging must outlive the copies
   if (e != hipSuccess) return hip_fail(m, e, "cold_load_weights: synchronize");
   m->arena_ptr = A;
@@ -633,7 +657,14 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
                                                m->widths[n_separate - 1]);
   const void *in = W + wl.X;
   unsigned char *bufs[2] = {W + wl.actA, W + wl.actB};
-  for (int l = 0; l < n_separate - (dense_tail ? 1 : 0); ++l) {
+  const int l0 = net_first(*m);
+  const bool net_rows = l0 >= 0 && net_rows_chosen(R);
+  TailArgs tail{};
+  if (fuse_tail)
+    tail = {A + al.w[L - 3], reinterpret_cast<const float *>(A + al.b[L - 3]), A + al.w[L - 2],
+            reinterpret_cast<const float *>(A + al.b[L - 2]), A + al.w[L - 1],
+            reinterpret_cast<const float *>(A + al.b[L - 1]), m->widths[L]};
+  for (int l = 0; l < (net_rows ? l0 : n_separate - (dense_tail ? 1 : 0)); ++l) {
     void *outp = bufs[l & 1];
     if ((e = marks.mark(l < 12 ? kDenseNames[l] : "dense")) != hipSuccess)
       return hip_fail(m, e, "profile event");
@@ -649,15 +680,26 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
     if (e != hipSuccess) return hip_fail(m, e, "dense layer launch");
     in = outp;
   }
-  if (dense_tail) {
+  if (net_rows) {
+    const int nl = net_layers(*m);
+    auto bias = [&](int i) { return reinterpret_cast<const float *>(A + al.b[l0 + i]); };
+    NetRowsArgs na{};
+    na.x = in;
+    na.w0 = A + al.wf[0]; na.b0 = bias(0);
+    if (nl == 3) na.w1 = A + al.wf[1], na.b1 = bias(1);
+    na.w2 = A + al.wf[nl - 1]; na.b2 = bias(nl - 1);
+    na.tail = tail;
+    na.scores = scores;
+    na.R = R;
+    na.K0 = m->widths[l0];
+    if ((e = marks.mark("net")) != hipSuccess) return hip_fail(m, e, "profile event");
+    if ((e = launch_net_rows(m->dtype, m->widths[l0 + 1], nl == 3 ? m->widths[l0 + 2] : 0, na, s)) != hipSuccess)
+      return hip_fail(m, e, "network launch");
+  } else if (dense_tail) {
     const int l = n_separate - 1;
     if ((e = marks.mark("dense_tail")) != hipSuccess) return hip_fail(m, e, "profile event");
     if ((e = launch_dense_tail(m->dtype, in, A + al.w[l], reinterpret_cast<const float *>(A + al.b[l]),
-                               m->widths[l + 1], m->widths[l], A + al.w[L - 3],
-                               reinterpret_cast<const float *>(A + al.b[L - 3]), A + al.w[L - 2],
-                               reinterpret_cast<const float *>(A + al.b[L - 2]), A + al.w[L - 1],
-                               reinterpret_cast<const float *>(A + al.b[L - 1]), m->widths[L],
-                               scores, R, s)) != hipSuccess)
+                               m->widths[l + 1], m->widths[l], tail, scores, R, s)) != hipSuccess)
       return hip_fail(m, e, "dense + tail launch");
   } else if (fuse_tail) {
     if ((e = marks.mark("tail")) != hipSuccess) return hip_fail(m, e, "profile event");

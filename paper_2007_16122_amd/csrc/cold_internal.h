@@ -304,8 +304,8 @@ __device__ void build_row_tiles(const int32_t *__restrict__ req_off, int64_t Q, 
   if (tid == 0) n_tiles[0] = (int32_t)(start0 < cap ? start0 : cap);
 }
 
-// rows of the tile launch_dense_relu_grouped uses for R rows, N outputs and K inputs
-int dense_grouped_tile_rows(int64_t R, int32_t N, int32_t K);
+// rows of the tile launch_dense_relu_grouped uses for R rows and N outputs
+int dense_grouped_tile_rows(int64_t R, int32_t N);
 // Y = ReLU(X W_q^T + b) where row r of X [R][K] belongs to request q(r)
 // and W_q = W + q * N * K; the row tiles, which never straddle two
 // requests, come from the table and count that launch_apply_compact built
@@ -328,7 +328,9 @@ hipError_t launch_dense_relu_grouped(int dtype, const void *x, const void *w, co
                                      RowTile *tiles, int32_t *n_tiles, hipStream_t s);
 bool tail_supported(int dtype, int K0, int N1, int N2, int n_out);
 // the fused tail reads its two hidden layers' weights fragment-major
-// (mlp.hip, frag_offset): [N][K] row-major -> that order (N % 16 == 0, K % 32 == 0)
+// (mlp_tile.h, frag_offset): [N][K] row-major -> that order (N % 16 == 0, K % 8 == 0;
+// (K rounded up to it, the added columns zero; frag_bytes of storage)
+inline size_t frag_bytes(int64_t N, int64_t K) { return (size_t)(N * ((K + 31) / 32 * 32) * 2); }
 hipError_t launch_pack_frag(const void *src, void *dst, int64_t N, int32_t K, hipStream_t s);
 hipError_t launch_mlp_tail(int dtype, const void *a, const void *w1, const float *b1,
                            const void *w2, const float *b2, const void *wh, const float *bh,
@@ -336,11 +338,33 @@ hipError_t launch_mlp_tail(int dtype, const void *a, const void *w1, const float
 // the last separate hidden layer (N = 256, the tail's input) and the fused
 // tail in one kernel; hipErrorNotSupported unless N == 256, K % 64 == 0 and
 // the model is in half precision
+// parameters of the fused tail: its two hidden layers (fragment-major
+// weights) and the head
+struct TailArgs {
+  const void *w1;
+  const float *b1;
+  const void *w2;
+  const float *b2;
+  const void *wh;
+  const float *bh;
+  int32_t n_out;
+};
 bool dense_tail_supported(int dtype, int64_t R, int32_t N, int32_t K);
 hipError_t launch_dense_tail(int dtype, const void *x, const void *w, const float *b, int32_t N,
-                             int32_t K, const void *w1, const float *b1, const void *w2,
-                             const float *b2, const void *wh, const float *bh, int32_t n_out,
-                             float *scores, int64_t R, hipStream_t s);
+                             int32_t K, const TailArgs &t, float *scores, int64_t R, hipStream_t s);
+// the whole network over 64-row tiles in one kernel (net_rows.hip)
+struct NetRowsArgs {
+  const void *x;          // [R][K0]
+  const void *w0, *w1, *w2;   // fragment-major; w1 only with three separate layers
+  const float *b0, *b1, *b2;
+  TailArgs tail;
+  float *scores;
+  int64_t R, tiles;
+  int32_t K0;
+};
+bool net_rows_shape(int dtype, const int32_t *widths, int32_t n_layers);
+bool net_rows_chosen(int64_t R);
+hipError_t launch_net_rows(int dtype, int32_t n0, int32_t n1, NetRowsArgs a, hipStream_t s);
 hipError_t launch_dense_f32(const float *x, const float *w, const float *b, float *y, int64_t R,
                             int32_t N, int32_t K, int act, hipStream_t s);
 hipError_t launch_topn(const float *scores, const float *bids, const int32_t *req_off, int64_t Q,

@@ -2200,7 +2200,7 @@ static hipError_t apply_compact_t(bool ll, const void *Xraw, void *Xc, const flo
   const int64_t n_apply = (R + kApplyRows - 1) / kApplyRows;
   const int64_t blocks = n_apply + Q * (int64_t)N + 1;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const int BR = dense_grouped_tile_rows(R, N, kp * d);
+  const int BR = dense_grouped_tile_rows(R, N);
   const int64_t cap = row_tiles_bound(R, Q, BR);
   const dim3 grid((unsigned)blocks);
   if (ll)

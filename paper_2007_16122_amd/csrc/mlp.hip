@@ -12,8 +12,6 @@
 //                   (workgroup i is dispatched to XCD i mod 8) and reuse it
 //                   from that XCD's L2.  256 x 256 tiles (8 waves) for large
 //                   batches, 64 x 64 for a single request.
-//  dense_relu_mfma  the same layer with register-staged, double-buffered LDS
-//                   tiles; used when K is not a multiple of 32.
 //  dense_tail       the last separate hidden layer (512 -> 256) fused with
 //                   the tail: the last two hidden layers and the head, with
 //                   the tail's activations carried at about twice the
@@ -25,26 +23,11 @@
 #include <type_traits>
 
 #include "cold_internal.h"
+#include "mlp_tile.h"
 
 namespace cold {
 
 constexpr int kBK = 32;    // K per step (one MFMA depth)
-constexpr int kPad = 8;    // elements of row padding in LDS
-constexpr int kLdsRow = kBK + kPad;
-
-template <typename TS> struct Mfma;
-template <> struct Mfma<__bf16> {
-  typedef bf16x8 frag;
-  __device__ static inline f32x4 mac(const frag &a, const frag &b, const f32x4 &c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct Mfma<_Float16> {
-  typedef f16x8 frag;
-  __device__ static inline f32x4 mac(const frag &a, const frag &b, const f32x4 &c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-  }
-};
 
 // XCD-aware tile order: workgroup b runs on XCD b % 8; give XCD x the
 // contiguous tile range [start_x, start_x + count_x).
@@ -53,122 +36,6 @@ __device__ __forceinline__ int xcd_tile(int b, int total) {
   const int base = total >> 3, extra = total & 7;
   const int start = x * base + (x < extra ? x : extra);
   return start + slot;
-}
-
-// Block tile BR rows x BN output features, 4 waves as 2 x 2, each wave
-// (BR/2) x (BN/2).  Per 32-deep K step a wave reads BR/32 + BN/32 fragments
-// of 16 bytes per lane and issues (BR/32)*(BN/32) MFMAs.
-template <typename TS, int BR, int BN>
-__global__ __launch_bounds__(256, 2) void dense_relu_mfma_kernel(const TS *__restrict__ X,
-                                                                 const TS *__restrict__ W,
-                                                                 const float *__restrict__ bias,
-                                                                 TS *__restrict__ Y, int64_t R, int N,
-                                                                 int K, int tiles_n, int tiles_total) {
-  typedef typename Mfma<TS>::frag frag;
-  constexpr int NI = BN / 32;              // 16-wide feature blocks per wave
-  constexpr int RJ = BR / 32;              // 16-wide row blocks per wave
-  constexpr int A_PER_T = BN * kBK / 8 / 256;   // 16-byte chunks of the W tile per thread
-  constexpr int B_PER_T = BR * kBK / 8 / 256;
-  static_assert(A_PER_T >= 1 && B_PER_T >= 1, "tile/thread mismatch");
-
-  __shared__ __align__(16) TS sA[2][BN * kLdsRow];
-  __shared__ __align__(16) TS sB[2][BR * kLdsRow];
-
-  const int tile = xcd_tile(blockIdx.x, tiles_total);
-  const int tr = tile / tiles_n, tn = tile - tr * tiles_n;
-  const int64_t r0 = (int64_t)tr * BR;
-  const int n0 = tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wn = wave & 1, wr = wave >> 1;
-
-  uint4 ra[A_PER_T], rb[B_PER_T];
-  auto load_global = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < A_PER_T; ++u) {
-      const int c = tid + 256 * u, row = c >> 2, kc = (c & 3) * 8;
-      const int n = n0 + row, k = k0 + kc;
-      ra[u] = (n < N && k < K) ? *reinterpret_cast<const uint4 *>(W + (int64_t)n * K + k)
-                               : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < B_PER_T; ++u) {
-      const int c = tid + 256 * u, row = c >> 2, kc = (c & 3) * 8;
-      const int64_t r = r0 + row;
-      const int k = k0 + kc;
-      rb[u] = (r < R && k < K) ? *reinterpret_cast<const uint4 *>(X + r * K + k)
-                               : make_uint4(0, 0, 0, 0);
-    }
-  };
-  auto store_lds = [&](int buf) {
-#pragma unroll
-    for (int u = 0; u < A_PER_T; ++u) {
-      const int c = tid + 256 * u, row = c >> 2, kc = (c & 3) * 8;
-      *reinterpret_cast<uint4 *>(&sA[buf][row * kLdsRow + kc]) = ra[u];
-    }
-#pragma unroll
-    for (int u = 0; u < B_PER_T; ++u) {
-      const int c = tid + 256 * u, row = c >> 2, kc = (c & 3) * 8;
-      *reinterpret_cast<uint4 *>(&sB[buf][row * kLdsRow + kc]) = rb[u];
-    }
-  };
-
-  f32x4 acc[NI][RJ];
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int j = 0; j < RJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int ksteps = (K + kBK - 1) / kBK;
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  const int frow = lane & 15, fk = (lane >> 4) * 8;
-  for (int ks = 0; ks < ksteps; ++ks) {
-    const int buf = ks & 1;
-    if (ks + 1 < ksteps) load_global((ks + 1) * kBK);
-    frag fa[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      fa[i] = *reinterpret_cast<const frag *>(&sA[buf][(wn * (BN / 2) + i * 16 + frow) * kLdsRow + fk]);
-#pragma unroll
-    for (int j = 0; j < RJ; ++j) {
-      const frag fb = *reinterpret_cast<const frag *>(&sB[buf][(wr * (BR / 2) + j * 16 + frow) * kLdsRow + fk]);
-#pragma unroll
-      for (int i = 0; i < NI; ++i) acc[i][j] = Mfma<TS>::mac(fa[i], fb, acc[i][j]);
-    }
-    if (ks + 1 < ksteps) store_lds(buf ^ 1);
-    __syncthreads();
-  }
-
-  // epilogue: lane holds D[4*(lane/16) + e][lane % 16], e = 0..3, of each block
-  const int dn = (lane >> 4) * 4, dr = lane & 15;
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int n = n0 + wn * (BN / 2) + i * 16 + dn;
-    if (n >= N) continue;
-    float bv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bv[e] = (n + e < N) ? bias[n + e] : 0.0f;
-#pragma unroll
-    for (int j = 0; j < RJ; ++j) {
-      const int64_t r = r0 + wr * (BR / 2) + j * 16 + dr;
-      if (r >= R) continue;
-      float o[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float t = acc[i][j][e] + bv[e];
-        o[e] = t > 0.0f ? t : 0.0f;
-      }
-      if (n + 3 < N) {
-        uint2 packed;
-        packed.x = (uint32_t)Elem<TS>::bits(o[0]) | ((uint32_t)Elem<TS>::bits(o[1]) << 16);
-        packed.y = (uint32_t)Elem<TS>::bits(o[2]) | ((uint32_t)Elem<TS>::bits(o[3]) << 16);
-        *reinterpret_cast<uint2 *>(Y + r * N + n) = packed;
-      } else {
-        for (int e = 0; e < 4 && n + e < N; ++e) Y[r * N + n + e] = Elem<TS>::from_f32(o[e]);
-      }
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -217,14 +84,6 @@ __device__ __forceinline__ void wait_stages(int later) {
 //    max(bits, 0) as signed integers is ReLU after rounding).
 // Waves are laid out 2 (rows) x WN (features); each wave owns a
 // (BR/2) x (BN/WN) block of 16 x 16 MFMA tiles.
-template <typename TS> struct Pair;
-template <> struct Pair<__bf16> {
-  typedef __bf16 v2 __attribute__((ext_vector_type(2)));
-};
-template <> struct Pair<_Float16> {
-  typedef _Float16 v2 __attribute__((ext_vector_type(2)));
-};
-
 // 16 bytes per lane from base + voff + soff into LDS at dst + 16 * lane;
 // reads at or past base + bytes return zeros
 __device__ __forceinline__ void buffer_load_lds16(const void *base, int bytes, void *dst, int voff,
@@ -234,19 +93,6 @@ __device__ __forceinline__ void buffer_load_lds16(const void *base, int bytes, v
   const __amdgpu_buffer_rsrc_t r =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, bytes, kRsrcWord3);
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)dst, 16, voff, soff, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t relu_bits2(uint32_t v) {
-  typedef short s2 __attribute__((ext_vector_type(2)));
-  const s2 r = __builtin_elementwise_max(__builtin_bit_cast(s2, v), (s2){0, 0});
-  return __builtin_bit_cast(uint32_t, r);
-}
-
-template <typename TS>
-__device__ __forceinline__ uint32_t round2(float lo, float hi) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  const typename Pair<TS>::v2 h = __builtin_convertvector((f2){lo, hi}, typename Pair<TS>::v2);
-  return __builtin_bit_cast(uint32_t, h);
 }
 
 // Tile geometry of the pipelined layer: BR x BN outputs over 2 x WN waves,
@@ -272,7 +118,7 @@ template <int BR, int BN, int S, int WN, int KB = 32> struct BufTile {
 // (i, j), i.e. output features n0 + wn*(BN/WN) + 16 i + 4 (lane/16) + e of row
 // r0 + wr*(BR/2) + 16 j + lane % 16.  smem holds the ring (RING bytes); on
 // return the ring is free once the workgroup has passed a barrier.
-template <typename TS, int BR, int BN, int S, int WN, int KB = 32, bool HALF = false>
+template <typename TS, int BR, int BN, int S, int WN, int KB = 32, bool RAGGED = false>
 __device__ __forceinline__ void buf_tile_kloop(
     const TS *__restrict__ X, const TS *__restrict__ W, const float *__restrict__ bias, int64_t R,
     int N, int K, int64_t r0, int n0, unsigned char *smem,
@@ -304,14 +150,26 @@ __device__ __forceinline__ void buf_tile_kloop(
     const int chunk = slot ^ swz(row & 15);
     voff[u] = (row * K + chunk * 8) * 2;
   }
+  // RAGGED (K not a multiple of KB): the last stage's chunks past the row's
+  // end are placed past the operand window, so they read zeros, and its
+  // 32-deep blocks past K are skipped; the sum runs over the same 32-deep
+  // blocks in the same order whatever KB is
+  const int ksteps = RAGGED ? (K + KB - 1) / KB : K / KB;
+  constexpr int kPastWindow = 0x40000000;
   auto issue = [&](int ks, int stage) {
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) {
       const int ins = wave * LOADS + u;
       const bool is_w = ins < BN / RPI;
+      int vo = voff[u];
+      if constexpr (RAGGED)
+        if (ks == ksteps - 1) {   // the same for every wave
+          const int row = (is_w ? ins : ins - BN / RPI) * RPI + lane / CPRW;
+          if (ks * KB + ((lane % CPRW) ^ swz(row & 15)) * 8 >= K) vo = kPastWindow;
+        }
       const int dst = is_w ? ins * RPI * ROWB : BN * ROWB + (ins - BN / RPI) * RPI * ROWB;
       buffer_load_lds16(is_w ? static_cast<const void *>(wbase) : static_cast<const void *>(xbase),
-                        is_w ? wbytes : xbytes, smem + stage * STAGE + dst, voff[u], ks * (KB * 2));
+                        is_w ? wbytes : xbytes, smem + stage * STAGE + dst, vo, ks * (KB * 2));
     }
   };
 
@@ -330,12 +188,6 @@ __device__ __forceinline__ void buf_tile_kloop(
     for (int j = 0; j < RJ; ++j) acc[i][j] = bv;
   }
 
-  // HALF (64-deep stages, K % 64 == 32): the last stage is a half stage;
-  // its second 32 of K lie past the rows' ends and are loaded (the next
-  // row's first elements, or zeros past the operand window) but not used,
-  // so the sum still runs over the same 32-deep K blocks in the same order
-  static_assert(!HALF || KB == 64, "half stages of 64-deep stages");
-  const int ksteps = HALF ? (K + KB - 1) / KB : K / KB;
 #pragma unroll
   for (int st = 0; st < S - 1; ++st)
     if (st < ksteps) issue(st, st);
@@ -363,8 +215,8 @@ __device__ __forceinline__ void buf_tile_kloop(
         const unsigned char *base = smem + st * STAGE;
 #pragma unroll
         for (int h = 0; h < KB / 32; ++h) {
-          if constexpr (HALF)
-            if (h > 0 && ks == ksteps - 1) break;   // the same for every wave
+          if constexpr (RAGGED)
+            if (h > 0 && ks * KB + h * 32 >= K) break;   // the same for every wave
           frag fa[NI], fb[RJ];
 #pragma unroll
           for (int i = 0; i < NI; ++i)
@@ -400,7 +252,7 @@ __device__ __forceinline__ void buf_tile_kloop(
 // whose weights start w_stride elements after the previous request's), and
 // workgroups past the table's count have no tile.
 template <typename TS, int BR, int BN, int S, int WN = 2, int MINW = 2, int KB = 32, bool GRP = false,
-          bool HALF = false>
+          bool RAGGED = false>
 __global__ __launch_bounds__(128 * WN, MINW) void dense_relu_buf_kernel(const TS *__restrict__ X,
                                                                      const TS *__restrict__ W,
                                                                      const float *__restrict__ bias,
@@ -438,7 +290,7 @@ __global__ __launch_bounds__(128 * WN, MINW) void dense_relu_buf_kernel(const TS
   const int dn = (lane >> 4) * 4, dr = lane & 15;
 
   f32x4 acc[NI][RJ];
-  buf_tile_kloop<TS, BR, BN, S, WN, KB, HALF>(X, Wt, bias, R, N, K, r0, n0, smem, acc);
+  buf_tile_kloop<TS, BR, BN, S, WN, KB, RAGGED>(X, Wt, bias, R, N, K, r0, n0, smem, acc);
 
   // epilogue: round, ReLU, stage the tile in LDS, write rows with 16-byte
   // stores.
@@ -481,31 +333,25 @@ __global__ __launch_bounds__(128 * WN, MINW) void dense_relu_buf_kernel(const TS
   }
 }
 
-// Fragment-major weights of the fused tail: a [N][K] matrix (N % 16 == 0,
-// K % 32 == 0) stored as one 1 KB block per (16-feature block fb, 32-deep K
-// step k), in MFMA operand order: lane l holds features fb*16 + l % 16, K
-// elements 32 k + 8 (l / 16) .. + 8.  A wave then loads a fragment as one
-// contiguous 1 KB block instead of 16 half-used cache lines.
-__host__ __device__ inline int64_t frag_offset(int fb, int k, int ksteps, int lane) {
-  return ((int64_t)(fb * ksteps + k) * 64 + lane) * 8;
-}
-
-// one 16-byte chunk per thread: row-major chunk (n, k..k+7) to its fragment-major place
+// one 16-byte chunk per thread: row-major chunk (n, k..k+7) to its
+// fragment-major place; chunks past K (to the whole 32-deep step) are zero
 __global__ __launch_bounds__(256) void pack_frag_kernel(const uint4 *__restrict__ src,
                                                         uint4 *__restrict__ dst, int64_t N, int32_t K) {
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t cpr = K / 8;
+  const int ks = (K + 31) / 32;
+  const int64_t cpr = 4 * ks;
   if (c >= N * cpr) return;
   const int64_t n = c / cpr;
   const int k = (int)(c - n * cpr) * 8;
   const int lane = ((k & 31) >> 3) * 16 + (int)(n & 15);
-  dst[frag_offset((int)(n >> 4), k >> 5, K / 32, lane) / 8] = src[c];
+  dst[frag_offset((int)(n >> 4), k >> 5, ks, lane) / 8] =
+      k < K ? src[(n * K + k) / 8] : make_uint4(0, 0, 0, 0);
 }
 
 hipError_t launch_pack_frag(const void *src, void *dst, int64_t N, int32_t K, hipStream_t s) {
   if (N <= 0) return hipSuccess;
-  if (N % 16 != 0 || K % 32 != 0) return hipErrorInvalidValue;
-  const int64_t chunks = N * (K / 8);
+  if (N % 16 != 0 || K % 8 != 0) return hipErrorInvalidValue;
+  const int64_t chunks = N * ((K + 31) / 32 * 4);
   hipLaunchKernelGGL(pack_frag_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s,
                      static_cast<const uint4 *>(src), static_cast<uint4 *>(dst), N, K);
   return hipGetLastError();
@@ -528,122 +374,6 @@ hipError_t launch_pack_frag(const void *src, void *dst, int64_t N, int32_t K, hi
 // summed in fp32. The last hidden layer's output stays in fp32 and the head
 // reads it as such. Every sum of the tail runs in the same order whichever
 // kernel, tile shape or wave computes it.
-
-// the two storage-type values packed in one 32-bit word, widened to fp32
-template <typename TS> __device__ __forceinline__ void unpack2(uint32_t w, float &a, float &b);
-template <> __device__ __forceinline__ void unpack2<__bf16>(uint32_t w, float &a, float &b) {
-  a = __uint_as_float(w << 16);
-  b = __uint_as_float(w & 0xFFFF0000u);
-}
-template <> __device__ __forceinline__ void unpack2<_Float16>(uint32_t w, float &a, float &b) {
-  a = static_cast<float>(__builtin_bit_cast(_Float16, (uint16_t)(w & 0xFFFFu)));
-  b = static_cast<float>(__builtin_bit_cast(_Float16, (uint16_t)(w >> 16)));
-}
-
-// hi/lo pairs of two fp32 values (see above); a value whose hi is not finite
-// (beyond the storage range) gets lo = 0
-template <typename TS>
-__device__ __forceinline__ void split2(float v0, float v1, uint32_t &hi, uint32_t &lo) {
-  hi = round2<TS>(v0, v1);
-  float h0, h1;
-  unpack2<TS>(hi, h0, h1);
-  const float d0 = __builtin_isfinite(h0) ? v0 - h0 : 0.0f;
-  const float d1 = __builtin_isfinite(h1) ? v1 - h1 : 0.0f;
-  lo = round2<TS>(d0, d1);
-}
-
-// MFMA sums of one tail layer on rows held in LDS: acc[i][j] = sum over K of
-// W[n][k] in[r][k] for the 16-row blocks jb0 .. jb0 + JB - 1 and the
-// NB 16-feature blocks of wf, from zero, K steps in order. in_at(row, c) is
-// the LDS address of 16-byte chunk c of an input row; with EXT the low halves
-// of the input sit lo_bytes after the high halves, and each K step adds
-// W hi, then W lo. wf[k][i] is the weight fragment of feature block i and K
-// step k.
-template <typename TS, int KS, int NB, int JB, bool EXT, typename InAt>
-__device__ __forceinline__ void tail_mma(const InAt &in_at, int lo_bytes,
-                                         const typename Mfma<TS>::frag (&wf)[KS][NB], int jb0,
-                                         int lane, f32x4 (&acc)[NB][JB]) {
-  typedef typename Mfma<TS>::frag frag;
-  const int frow = lane & 15, fq = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < JB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < KS; ++k) {
-#pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      const TS *p = in_at((jb0 + j) * 16 + frow, 4 * k + fq);
-      const frag fb = *reinterpret_cast<const frag *>(p);
-      frag fl;
-      if constexpr (EXT) fl = *reinterpret_cast<const frag *>(reinterpret_cast<const char *>(p) + lo_bytes);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        acc[i][j] = Mfma<TS>::mac(wf[k][i], fb, acc[i][j]);
-        if constexpr (EXT) acc[i][j] = Mfma<TS>::mac(wf[k][i], fl, acc[i][j]);
-      }
-    }
-  }
-}
-
-// bias, ReLU, then the hi/lo pair of every output: row (jb0 + j) * 16 + lane % 16,
-// features (nb0 + i) * 16 + 4 (lane / 16) .. + 3; the low halves go lo_elems
-// elements after the high halves
-template <typename TS, int NB, int JB>
-__device__ __forceinline__ void tail_store_ext(const f32x4 (&acc)[NB][JB], const float *__restrict__ bg,
-                                               TS *out, int stride, int lo_elems, int nb0, int jb0,
-                                               int lane) {
-  const int dn = (lane >> 4) * 4, dr = lane & 15;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int n = (nb0 + i) * 16 + dn;
-    float bv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bv[e] = bg[n + e];
-#pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float t = acc[i][j][e] + bv[e];
-        v[e] = t > 0.0f ? t : 0.0f;
-      }
-      uint2 hi, lo;
-      split2<TS>(v[0], v[1], hi.x, lo.x);
-      split2<TS>(v[2], v[3], hi.y, lo.y);
-      TS *o = out + ((jb0 + j) * 16 + dr) * stride + n;
-      *reinterpret_cast<uint2 *>(o) = hi;
-      *reinterpret_cast<uint2 *>(o + lo_elems) = lo;
-    }
-  }
-}
-
-// bias and ReLU in fp32, stored as fp32 (the last hidden layer)
-template <int NB, int JB>
-__device__ __forceinline__ void tail_store_f32(const f32x4 (&acc)[NB][JB], const float *__restrict__ bg,
-                                               float *out, int stride, int nb0, int jb0, int lane) {
-  const int dn = (lane >> 4) * 4, dr = lane & 15;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int n = (nb0 + i) * 16 + dn;
-    float bv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bv[e] = bg[n + e];
-#pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      float4 v;
-      v.x = acc[i][j][0] + bv[0];
-      v.y = acc[i][j][1] + bv[1];
-      v.z = acc[i][j][2] + bv[2];
-      v.w = acc[i][j][3] + bv[3];
-      v.x = v.x > 0.0f ? v.x : 0.0f;
-      v.y = v.y > 0.0f ? v.y : 0.0f;
-      v.z = v.z > 0.0f ? v.z : 0.0f;
-      v.w = v.w > 0.0f ? v.w : 0.0f;
-      *reinterpret_cast<float4 *>(out + ((jb0 + j) * 16 + dr) * stride + n) = v;
-    }
-  }
-}
 
 // Output head of the fused tail on fp32 rows: 4 threads per row (row tid / 4),
 // each summing a quarter of the N2 inputs in order, then two shuffle steps;
@@ -749,7 +479,11 @@ __global__ __launch_bounds__(256, 2) void mlp_tail_kernel(const TS *__restrict__
   auto in0 = [&](int row, int c) { return s_in + row * S0 + c * 8; };
   f32x4 a1[NB1][BR / 16];
   tail_mma<TS, KS1, NB1, BR / 16, false>(in0, 0, w1f, 0, lane, a1);
-  tail_store_ext<TS, NB1, BR / 16>(a1, b1, s_h1, S1, BR * S1, wave * NB1, 0, lane);
+  float4 bv1[NB1];
+#pragma unroll
+  for (int i = 0; i < NB1; ++i)
+    bv1[i] = *reinterpret_cast<const float4 *>(b1 + (wave * NB1 + i) * 16 + (lane >> 4) * 4);
+  tail_store_ext<TS, NB1, BR / 16>(a1, bv1, s_h1, S1, BR * S1, wave * NB1, 0, lane);
   __syncthreads();   // the input tile is dead: the last hidden tile takes its place
   auto in1 = [&](int row, int c) { return s_h1 + row * S1 + c * 8; };
   f32x4 a2[NB2][BR / 16];
@@ -776,34 +510,27 @@ __global__ __launch_bounds__(256, 2) void mlp_tail_kernel(const TS *__restrict__
 template <typename TS, int BR, int MINB, int WN = 4, int KB = 64, int S = 2>
 __global__ __launch_bounds__(128 * WN, MINB) void dense_tail_kernel(
     const TS *__restrict__ X, const TS *__restrict__ W, const float *__restrict__ bias, int64_t R,
-    int K, int tiles_total, const TS *__restrict__ W1, const float *__restrict__ b1,
-    const TS *__restrict__ W2, const float *__restrict__ b2, const TS *__restrict__ Wh,
-    const float *__restrict__ bh, int n_out, float *__restrict__ scores) {
-  typedef typename Mfma<TS>::frag frag;
+    int K, int tiles_total, TailArgs t, float *__restrict__ scores) {
   constexpr int BN = 256;
   typedef BufTile<BR, BN, S, WN, KB> G;
   constexpr int NI = G::NI, RJ = G::RJ, NT = G::NT;
-  constexpr int N1 = 128, N2 = 64;                     // tail widths
-  constexpr int S1 = N1 + 8, S2 = N2 + 4;              // padded LDS rows of the tail
-  constexpr int HROW = BN * 2;                         // bytes per row of the layer's output
-  constexpr int KS1 = BN / 32, KS2 = N1 / 32;
+  constexpr int N2 = kTailN2;
+  constexpr int HROW = kTailHRow;                      // bytes per row of the layer's output
   // rows per pass: as many as the ring holds as hi/lo pairs, at most 128
   constexpr int PR = BR <= 128 && 2 * BR * HROW <= G::RING ? BR : (2 * 128 * HROW <= G::RING ? 128 : 64);
   constexpr int NP = BR / PR, JP = RJ / NP;            // passes; row blocks of a wave per pass
   constexpr int RH = G::NW / 4;                        // row groups of the tail layers
   constexpr int JB = PR / RH / 16;                     // row blocks of a wave in the tail layers
   constexpr int H3_BYTES = 2 * PR * HROW;              // hi and lo of the layer's output
-  constexpr int H1_BYTES = 2 * PR * S1 * 2, H2_BYTES = PR * S2 * 4;
   // head weights in the ring when it has room past the layer's output
   constexpr bool WH_IN_RING = G::RING >= H3_BYTES + 2 * N2 * 4 + 16;
   static_assert(G::RING >= H3_BYTES, "a pass of the layer's output takes the ring");
   static_assert(G::NW == 4 || G::NW == 8, "the tail layers split 4 (features) x NW / 4 (rows)");
-  static_assert(H1_BYTES + H2_BYTES <= H3_BYTES, "both hidden tiles fit where the layer's output was");
+  static_assert(tail_lds_bytes(PR) <= H3_BYTES, "both hidden tiles fit where the layer's output was");
   static_assert(RJ % NP == 0 && PR * 4 <= NT && JB >= 1, "passes");
   __shared__ __align__(16) unsigned char smem[G::RING];
   __shared__ float s_whb_own[WH_IN_RING ? 1 : 2 * N2 + 4];
   float *s_wh = WH_IN_RING ? reinterpret_cast<float *>(smem + H3_BYTES) : s_whb_own;
-  float *s_bh = s_wh + 2 * N2;
 
   const int tile = xcd_tile(blockIdx.x, tiles_total);
   const int64_t r0 = (int64_t)tile * BR;
@@ -811,134 +538,40 @@ __global__ __launch_bounds__(128 * WN, MINB) void dense_tail_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave % WN, wr = wave / WN;
 
-  // tail weights: wave w owns feature blocks 2 (w % 4) and 2 (w % 4) + 1 of
-  // the first tail layer, and feature block w % 4 of the second, each on
-  // the rows PR/2 (w / 4) .. PR/2 (w / 4 + 1) of a pass. With few
-  // accumulators they are loaded before the K loop, so their latency hides
-  // behind it (the loads are older than the ring's, which the K loop's
-  // counted waits allow for); with many, after it.
+  // with few accumulators the tail's weights are loaded before the K loop, so
+  // their latency hides behind it (the loads are older than the ring's, which
+  // the K loop's counted waits allow for); with many, after it
   constexpr bool W_EARLY = NI * RJ <= 8;
-  frag w1f[KS1][2], w2f[KS2][1];
-  float whv, bhv;
-  auto load_tail_weights = [&]() {
-#pragma unroll
-    for (int k = 0; k < KS1; ++k)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        w1f[k][i] = *reinterpret_cast<const frag *>(W1 + frag_offset(2 * (wave % 4) + i, k, KS1, lane));
-#pragma unroll
-    for (int k = 0; k < KS2; ++k)
-      w2f[k][0] = *reinterpret_cast<const frag *>(W2 + frag_offset(wave % 4, k, KS2, lane));
-    whv = Elem<TS>::to_f32(Wh[tid < n_out * N2 ? tid : 0]);
-    bhv = bh[tid < n_out ? tid : 0];
-  };
-  if constexpr (W_EARLY) load_tail_weights();
+  TailWeights<TS> tw;
+  if constexpr (W_EARLY) {
+    tw.load(t, wave, lane, tid);
+    tw.load_bias(t, wave, lane);
+  }
 
   f32x4 acc[NI][RJ];
   buf_tile_kloop<TS, BR, BN, S, WN, KB>(X, W, bias, R, BN, K, r0, 0, smem, acc);
-  if constexpr (!W_EARLY) load_tail_weights();
+  if constexpr (!W_EARLY) tw.load(t, wave, lane, tid);
   compiler_fence();
   __builtin_amdgcn_s_barrier();   // every wave is past the K loop: the ring is free
   compiler_fence();
-  if (tid < n_out * N2) s_wh[tid] = whv;
-  if (tid < n_out) s_bh[tid] = bhv;
+  tw.put_head(s_wh, t.n_out, tid);
 
   const int dn = (lane >> 4) * 4, dr = lane & 15;
-  TS *s_h1 = reinterpret_cast<TS *>(smem);
-  float *s_h2 = reinterpret_cast<float *>(smem + H1_BYTES);
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    // this pass's rows of the layer's output: bias (in the accumulators),
-    // ReLU, hi/lo pairs into the LDS
+    // this pass's rows of the layer's output
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int n = wn * (BN / WN) + i * 16 + dn;
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int jj = 0; jj < JP; ++jj) {
-        const int j = p * JP + jj;
-        const int rl = wr * (PR / 2) + jj * 16 + dr;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e] > 0.0f ? acc[i][j][e] : 0.0f;
-        uint2 hi, lo;
-        split2<TS>(v[0], v[1], hi.x, lo.x);
-        split2<TS>(v[2], v[3], hi.y, lo.y);
-        unsigned char *o = smem + rl * HROW + (((n >> 3) ^ (rl & 7)) << 4) + (n & 7) * 2;
-        *reinterpret_cast<uint2 *>(o) = hi;
-        *reinterpret_cast<uint2 *>(o + PR * HROW) = lo;
-      }
-    }
+      for (int jj = 0; jj < JP; ++jj)
+        tail_put_pair<TS, PR>(acc[i][p * JP + jj], smem, wn * (BN / WN) + i * 16 + dn,
+                              wr * (PR / 2) + jj * 16 + dr);
     __syncthreads();   // the pass's tile (and the head weights) are in the LDS
-
-    // first tail layer (each wave reads its row group of the pass once for
-    // its two feature blocks); the tile is dead once every wave has its
-    // sums, and the layer's output takes its place
-    auto in0 = [&](int row, int c) {
-      return reinterpret_cast<const TS *>(smem + row * HROW + ((c ^ (row & 7)) << 4));
-    };
-    f32x4 a1[2][JB];
-    tail_mma<TS, KS1, 2, JB, true>(in0, PR * HROW, w1f, (wave / 4) * JB, lane, a1);
-    __syncthreads();
-    tail_store_ext<TS, 2, JB>(a1, b1, s_h1, S1, PR * S1, 2 * (wave % 4), (wave / 4) * JB, lane);
-    __syncthreads();
-    // second tail layer (wave w: feature block fb = w % 4 over its row
-    // group), bias and ReLU in fp32, and the head's sums over the block's 16
-    // features straight from the accumulators: lane (c, q) holds features
-    // 16 fb + 4 q + e of row c; its four products are added in e order, the
-    // four quarters by two shuffles; the feature blocks' sums meet in LDS
-    auto in1 = [&](int row, int c) { return s_h1 + row * S1 + c * 8; };
-    f32x4 a2[1][JB];
-    tail_mma<TS, KS2, 1, JB, true>(in1, PR * S1 * 2, w2f, (wave / 4) * JB, lane, a2);
-    {
-      const int fb = wave % 4, q4 = lane >> 4;
-      float wz0[4], wz1[4], bb[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = 16 * fb + 4 * q4 + e;
-        wz0[e] = s_wh[k];
-        wz1[e] = n_out > 1 ? s_wh[N2 + k] : 0.0f;
-        bb[e] = b2[k];
-      }
-#pragma unroll
-      for (int j = 0; j < JB; ++j) {
-        float z0 = 0.0f, z1 = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float v = a2[0][j][e] + bb[e];
-          v = v > 0.0f ? v : 0.0f;
-          z0 += wz0[e] * v;
-          z1 += wz1[e] * v;
-        }
-        z0 += __shfl_xor(z0, 16);
-        z0 += __shfl_xor(z0, 32);
-        z1 += __shfl_xor(z1, 16);
-        z1 += __shfl_xor(z1, 32);
-        if (q4 == 0) {
-          const int lr = ((wave / 4) * JB + j) * 16 + dr;
-          s_h2[(fb * PR + lr) * 2] = z0;
-          s_h2[(fb * PR + lr) * 2 + 1] = z1;
-        }
-      }
-    }
-    __syncthreads();
-    // head: the four blocks' sums in block order, then the bias; LDS row lr
-    // of the pass is row (lr / (PR/2)) * (BR/2) + p * (PR/2) + lr % (PR/2) of
-    // the tile
-    if (tid < PR) {
-      const int lr = tid;
-      float z0 = s_h2[lr * 2], z1 = s_h2[lr * 2 + 1];
-#pragma unroll
-      for (int fb = 1; fb < 4; ++fb) {
-        z0 += s_h2[(fb * PR + lr) * 2];
-        z1 += s_h2[(fb * PR + lr) * 2 + 1];
-      }
-      const int64_t r = r0 + (lr / (PR / 2)) * (BR / 2) + p * (PR / 2) + lr % (PR / 2);
-      if (r < R) {
-        z0 += s_bh[0];
-        if (n_out > 1) z1 += s_bh[1];
-        scores[r] = n_out == 1 ? 1.0f / (1.0f + expf(-z0)) : 1.0f / (1.0f + expf(z0 - z1));
-      }
-    }
+    // LDS row lr of the pass is row (lr / (PR/2)) * (BR/2) + p * (PR/2) +
+    // lr % (PR/2) of the tile
+    tail_rows<TS, PR, JB, true, !W_EARLY>(smem, smem, tw, t, s_wh, scores,
+                                [&](int lr) { return r0 + (lr / (PR / 2)) * (BR / 2) + p * (PR / 2) + lr % (PR / 2); },
+                                R, tid, lane, wave);
     if (p + 1 < NP) __syncthreads();   // the next pass overwrites the tail's tiles
   }
 }
@@ -1131,19 +764,6 @@ __global__ __launch_bounds__(256) void head_kernel(const TS *__restrict__ A, con
 }
 
 // ------------------------------------------------------------- launchers
-template <typename TS, int BR, int BN>
-static hipError_t dense_mfma_t(const void *x, const void *w, const float *b, void *y, int64_t R,
-                               int N, int K, hipStream_t s) {
-  const int tiles_n = (N + BN - 1) / BN;
-  const int64_t tiles_r = (R + BR - 1) / BR;
-  const int64_t total = tiles_r * tiles_n;
-  if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((dense_relu_mfma_kernel<TS, BR, BN>), dim3((unsigned)total), dim3(256), 0, s,
-                     static_cast<const TS *>(x), static_cast<const TS *>(w), b,
-                     static_cast<TS *>(y), R, N, K, tiles_n, (int)total);
-  return hipGetLastError();
-}
-
 // requests with weights of their own (see dense_relu_buf_kernel's GRP)
 struct GroupArgs {
   int64_t Q;
@@ -1152,7 +772,7 @@ struct GroupArgs {
   int64_t w_stride;
 };
 
-template <typename TS, int BR, int BN, int S, int WN, int MINW, int KB, bool HALF>
+template <typename TS, int BR, int BN, int S, int WN, int MINW, int KB, bool RAGGED>
 static hipError_t dense_buf_launch(const void *x, const void *w, const float *b, void *y, int64_t R,
                                    int N, int K, hipStream_t s, const GroupArgs *ga) {
   const int tiles_n = (N + BN - 1) / BN;
@@ -1160,12 +780,12 @@ static hipError_t dense_buf_launch(const void *x, const void *w, const float *b,
   const int64_t total = tiles_r * tiles_n;
   if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (ga) {
-    hipLaunchKernelGGL((dense_relu_buf_kernel<TS, BR, BN, S, WN, MINW, KB, true, HALF>), dim3((unsigned)total),
+    hipLaunchKernelGGL((dense_relu_buf_kernel<TS, BR, BN, S, WN, MINW, KB, true, RAGGED>), dim3((unsigned)total),
                        dim3(128 * WN), 0, s, static_cast<const TS *>(x), static_cast<const TS *>(w), b,
                        static_cast<TS *>(y), R, N, K, tiles_n, (int)total, ga->tiles, ga->n_tiles,
                        ga->w_stride);
   } else {
-    hipLaunchKernelGGL((dense_relu_buf_kernel<TS, BR, BN, S, WN, MINW, KB, false, HALF>), dim3((unsigned)total),
+    hipLaunchKernelGGL((dense_relu_buf_kernel<TS, BR, BN, S, WN, MINW, KB, false, RAGGED>), dim3((unsigned)total),
                        dim3(128 * WN), 0, s, static_cast<const TS *>(x), static_cast<const TS *>(w), b,
                        static_cast<TS *>(y), R, N, K, tiles_n, (int)total,
                        static_cast<const RowTile *>(nullptr), static_cast<const int32_t *>(nullptr),
@@ -1174,35 +794,31 @@ static hipError_t dense_buf_launch(const void *x, const void *w, const float *b,
   return hipGetLastError();
 }
 
-// 64-deep stages take the half-stage variant when K % 64 == 32
+// a K that is no multiple of the stage depth takes the ragged variant
 template <typename TS, int BR, int BN, int S, int WN, int MINW, int KB = 32>
 static hipError_t dense_buf_t(const void *x, const void *w, const float *b, void *y, int64_t R,
                               int N, int K, hipStream_t s, const GroupArgs *ga = nullptr) {
-  if constexpr (KB == 64) {
-    if (K % 64 != 0) return dense_buf_launch<TS, BR, BN, S, WN, MINW, 64, true>(x, w, b, y, R, N, K, s, ga);
-  }
+  if (K % KB != 0) return dense_buf_launch<TS, BR, BN, S, WN, MINW, KB, true>(x, w, b, y, R, N, K, s, ga);
   return dense_buf_launch<TS, BR, BN, S, WN, MINW, KB, false>(x, w, b, y, R, N, K, s, ga);
 }
 
-// The tile shape of a layer of R rows, N outputs and K inputs (the
-// buffered kernel for K % 32 == 0 and N % 8 == 0, else the plain one).
+// The tile shape of a layer of R rows, N outputs and K inputs (both
+// multiples of 8, as every half-precision model's are).
 //   Large batches: 256 x 256 tiles over 8 waves, in 64-deep stages (one
-// barrier per 64 MFMAs per wave, whole 128-byte rows per load; a last half
-// stage when K % 64 == 32), or 256 x 128 and 256 x 64 over 4 waves in
+// barrier per 64 MFMAs per wave, whole 128-byte rows per load; a shorter
+// last stage when K is no multiple of 64), or 256 x 128 and 256 x 64 over 4 waves in
 // 32-deep stages for narrower layers; batches of a few thousand ads would
 // leave most CUs idle with those, so 128..192 x 128 tiles while 128-row
 // tiles would still number one per CU, else 64 x 64.
 //   Every tile shape sums the same 32-deep K blocks in the same order, so the
 // outputs do not depend on the shape.
 enum class DTile {
-  k192x128, k160x128, k128x128, k64x64_3s, k64x64, k256x256, k256x128, k256x64, kPlain128, kPlain64
+  k192x128, k160x128, k128x128, k64x64_3s, k64x64, k256x256, k256x128, k256x64
 };
 
-static DTile dense_tile(int64_t R, int N, int K) {
-  if (K % kBK != 0 || N % 8 != 0) return N % 128 == 0 ? DTile::kPlain128 : DTile::kPlain64;
+static DTile dense_tile(int64_t R, int N) {
   const int64_t big_tiles = ((R + 255) / 256) * ((N + 127) / 128);
   const int64_t mid_tiles = ((R + 127) / 128) * ((N + 127) / 128);
-  // 64-deep stages for every K here (K % 32 == 0; a half stage ends K % 64 == 32)
   const int64_t cus = device_cus() > 0 ? device_cus() : 256;
   if (big_tiles < 256 && mid_tiles >= 256 && N % 128 == 0) {
     // x 128 tiles with the row height that gives the least work to the
@@ -1246,7 +862,7 @@ static int dense_tile_rows(DTile t) {
 template <typename TS>
 static hipError_t dense_mfma_dt(const void *x, const void *w, const float *b, void *y, int64_t R,
                                 int N, int K, hipStream_t s, const GroupArgs *ga = nullptr) {
-  switch (dense_tile(R, N, K)) {
+  switch (dense_tile(R, N)) {
     case DTile::k192x128: return dense_buf_t<TS, 192, 128, 2, 2, 2, 64>(x, w, b, y, R, N, K, s, ga);
     case DTile::k160x128: return dense_buf_t<TS, 160, 128, 2, 2, 2, 64>(x, w, b, y, R, N, K, s, ga);
     case DTile::k128x128: return dense_buf_t<TS, 128, 128, 2, 2, 2, 64>(x, w, b, y, R, N, K, s, ga);
@@ -1254,19 +870,14 @@ static hipError_t dense_mfma_dt(const void *x, const void *w, const float *b, vo
     case DTile::k64x64: return dense_buf_t<TS, 64, 64, 2, 2, 2, 64>(x, w, b, y, R, N, K, s, ga);
     case DTile::k256x256: return dense_buf_t<TS, 256, 256, 2, 4, 1, 64>(x, w, b, y, R, N, K, s, ga);
     case DTile::k256x128: return dense_buf_t<TS, 256, 128, 3, 2, 2>(x, w, b, y, R, N, K, s, ga);
-    case DTile::k256x64: return dense_buf_t<TS, 256, 64, 3, 2, 2>(x, w, b, y, R, N, K, s, ga);
-    case DTile::kPlain128:
-      if (ga) return hipErrorInvalidValue;
-      return dense_mfma_t<TS, 256, 128>(x, w, b, y, R, N, K, s);
-    default:
-      if (ga) return hipErrorInvalidValue;
-      return dense_mfma_t<TS, 256, 64>(x, w, b, y, R, N, K, s);
+    default: return dense_buf_t<TS, 256, 64, 3, 2, 2>(x, w, b, y, R, N, K, s, ga);
   }
 }
 
 hipError_t launch_dense_relu(int dtype, const void *x, const void *w, const float *b, void *y,
                              int64_t R, int32_t N, int32_t K, hipStream_t s) {
   if (R <= 0) return hipSuccess;
+  if (dtype != kF32 && (K % 8 != 0 || N % 8 != 0)) return hipErrorInvalidValue;
   if (dtype == kF32) {
     // fp32 models: the fp32 matrix cores when rows are whole 16-byte vectors
     if (K % 4 == 0)
@@ -1295,8 +906,8 @@ hipError_t launch_dense_relu_grouped(int dtype, const void *x, const void *w, co
   return dense_mfma_dt<_Float16>(x, w, b, y, R, N, K, s, &ga);
 }
 
-int dense_grouped_tile_rows(int64_t R, int32_t N, int32_t K) {
-  return dense_tile_rows(dense_tile(R, N, K));
+int dense_grouped_tile_rows(int64_t R, int32_t N) {
+  return dense_tile_rows(dense_tile(R, N));
 }
 
 bool tail_supported(int dtype, int K0, int N1, int N2, int n_out) {
@@ -1329,20 +940,14 @@ bool dense_tail_supported(int dtype, int64_t R, int32_t N, int32_t K) {
 
 template <typename TS, int BR, int MINB, int WN = 4, int KB = 64, int S = 2>
 static void launch_dense_tail_t(const void *x, const void *w, const float *b, int32_t K,
-                                const void *w1, const float *b1, const void *w2, const float *b2,
-                                const void *wh, const float *bh, int32_t n_out, float *scores,
-                                int64_t R, hipStream_t s) {
+                                const TailArgs &t, float *scores, int64_t R, hipStream_t s) {
   const int tiles = (int)((R + BR - 1) / BR);
   hipLaunchKernelGGL((dense_tail_kernel<TS, BR, MINB, WN, KB, S>), dim3(tiles), dim3(128 * WN), 0, s,
-                     static_cast<const TS *>(x), static_cast<const TS *>(w), b, R, K, tiles,
-                     static_cast<const TS *>(w1), b1, static_cast<const TS *>(w2), b2,
-                     static_cast<const TS *>(wh), bh, n_out, scores);
+                     static_cast<const TS *>(x), static_cast<const TS *>(w), b, R, K, tiles, t, scores);
 }
 
 hipError_t launch_dense_tail(int dtype, const void *x, const void *w, const float *b, int32_t N,
-                             int32_t K, const void *w1, const float *b1, const void *w2,
-                             const float *b2, const void *wh, const float *bh, int32_t n_out,
-                             float *scores, int64_t R, hipStream_t s) {
+                             int32_t K, const TailArgs &t, float *scores, int64_t R, hipStream_t s) {
   if (!dense_tail_supported(dtype, R, N, K)) return hipErrorNotSupported;
   // 256-row tiles over 8 waves while the separate layer would use 256 x 256
   // tiles (at least one tile per CU); for batches of many rounds of tiles,
@@ -1356,15 +961,15 @@ hipError_t launch_dense_tail(int dtype, const void *x, const void *w, const floa
   const bool rounds = (R + 127) / 128 >= 8 * (int64_t)cus;
   const bool few = (R + 63) / 64 < cus;
   if (dtype == kBF16) {
-    if (big && rounds) launch_dense_tail_t<__bf16, 128, 2, 2, 32, 3>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
-    else if (big) launch_dense_tail_t<__bf16, 256, 1>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
-    else if (few) launch_dense_tail_t<__bf16, 32, 2, 2>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
-    else launch_dense_tail_t<__bf16, 64, 2>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
+    if (big && rounds) launch_dense_tail_t<__bf16, 128, 2, 2, 32, 3>(x, w, b, K, t, scores, R, s);
+    else if (big) launch_dense_tail_t<__bf16, 256, 1>(x, w, b, K, t, scores, R, s);
+    else if (few) launch_dense_tail_t<__bf16, 32, 2, 2>(x, w, b, K, t, scores, R, s);
+    else launch_dense_tail_t<__bf16, 64, 2>(x, w, b, K, t, scores, R, s);
   } else {
-    if (big && rounds) launch_dense_tail_t<_Float16, 128, 2, 2, 32, 3>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
-    else if (big) launch_dense_tail_t<_Float16, 256, 1>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
-    else if (few) launch_dense_tail_t<_Float16, 32, 2, 2>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
-    else launch_dense_tail_t<_Float16, 64, 2>(x, w, b, K, w1, b1, w2, b2, wh, bh, n_out, scores, R, s);
+    if (big && rounds) launch_dense_tail_t<_Float16, 128, 2, 2, 32, 3>(x, w, b, K, t, scores, R, s);
+    else if (big) launch_dense_tail_t<_Float16, 256, 1>(x, w, b, K, t, scores, R, s);
+    else if (few) launch_dense_tail_t<_Float16, 32, 2, 2>(x, w, b, K, t, scores, R, s);
+    else launch_dense_tail_t<_Float16, 64, 2>(x, w, b, K, t, scores, R, s);
   }
   return hipGetLastError();
 }

@@ -489,6 +489,21 @@ int check_call(cold_model *m, const cold_batch *b, const float *scores, int32_t 
   return COLD_OK;
 }
 
+// End of a scoring call: the last stage mark and, when validating, the error bits.
+int finish(cold_model *m, StageMarks &marks, int32_t *err, bool validate, hipStream_t s) {
+  hipError_t e;
+  if ((e = marks.mark(nullptr)) != hipSuccess) return hip_fail(m, e, "profile event");
+  if (validate) {
+    int32_t flag = 0;
+    if ((e = hipMemcpyAsync(&flag, err, sizeof flag, hipMemcpyDeviceToHost, s)) != hipSuccess)
+      return hip_fail(m, e, "flag readback");
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(m, e, "synchronize");
+    if (flag) return fail(m, COLD_ERR_ID_RANGE, "out-of-range %s%s", (flag & 1) ? "ids " : "",
+                          (flag & 2) ? "offsets" : "");
+  }
+  return COLD_OK;
+}
+
 // The launch sequence of one scoring call on a checked batch, with the
 // workspace regions at W (work_layout(R, Q) bytes, 256-byte aligned).  With
 // profile, stage events are recorded when the model's profiling is on.
@@ -539,6 +554,19 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
   // top-k models with a compacted network input (the first layer per request)
   const bool compact = compact_input(*m);
   float *sb_compact = compact ? (importance ? importance : reinterpret_cast<float *>(W + wl.sbuf)) : nullptr;
+  // a small fp32 model runs in one kernel, whatever the batch
+  if (full && m->dtype == kF32 &&
+      net_f32_shape(m->M, m->H, m->d * m->es, D.n_seq, m->widths.data(), D.n_layers)) {
+    g.X = x_out;
+    g.s_buf = importance;
+    auto W_ = [&](int l) { return reinterpret_cast<const float *>(A + al.w[l]); };
+    auto B_ = [&](int l) { return reinterpret_cast<const float *>(A + al.b[l]); };
+    const NetF32Args n{W_(0), B_(0), W_(1), B_(1), W_(2), B_(2), scores,
+                       m->widths[1], m->widths[2], m->widths[3], m->hashed, D.linear_log};
+    if ((e = marks.mark("net_f32")) != hipSuccess) return hip_fail(m, e, "profile event");
+    if ((e = launch_net_f32(g, n, s)) != hipSuccess) return hip_fail(m, e, "network launch");
+    return finish(m, marks, g.err, validate, s);
+  }
   if (user_pool_needed(m->dtype, g)) {   // per-request user rows and pooled sequences
     if ((e = marks.mark("user_pool")) != hipSuccess) return hip_fail(m, e, "profile event");
     if ((e = launch_user_pool(m->dtype, m->hashed, g, s)) != hipSuccess)
@@ -714,16 +742,7 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
                          scores, R, m->widths[L - 1], m->widths[L], s)) != hipSuccess)
       return hip_fail(m, e, "head launch");
   }
-  if ((e = marks.mark(nullptr)) != hipSuccess) return hip_fail(m, e, "profile event");
-  if (validate) {
-    int32_t flag = 0;
-    if ((e = hipMemcpyAsync(&flag, g.err, sizeof flag, hipMemcpyDeviceToHost, s)) != hipSuccess)
-      return hip_fail(m, e, "flag readback");
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(m, e, "synchronize");
-    if (flag) return fail(m, COLD_ERR_ID_RANGE, "out-of-range %s%s", (flag & 1) ? "ids " : "",
-                          (flag & 2) ? "offsets" : "");
-  }
-  return COLD_OK;
+  return finish(m, marks, g.err, validate, s);
 }
 
 }  // namespace

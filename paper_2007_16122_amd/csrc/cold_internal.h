@@ -362,6 +362,18 @@ struct NetRowsArgs {
   int64_t R, tiles;
   int32_t K0;
 };
+// a small fp32 model (squeeze-form SE, two hidden layers of at most 64) in one
+// kernel, from the ids to the CTR (net_f32.hip); g as for the gathers, X
+// written only when g.X is not null
+struct NetF32Args {
+  const float *w1, *b1, *w2, *b2, *wh, *bh;
+  float *scores;
+  int32_t n1, n2, n_out;
+  int32_t hashed, linear_log;
+};
+bool net_f32_shape(int32_t M, int32_t H, int32_t row_bytes, int32_t n_seq, const int32_t *widths,
+                   int32_t n_layers);
+hipError_t launch_net_f32(const GatherArgs &g, const NetF32Args &n, hipStream_t s);
 bool net_rows_shape(int dtype, const int32_t *widths, int32_t n_layers);
 bool net_rows_chosen(int64_t R);
 hipError_t launch_net_rows(int dtype, int32_t n0, int32_t n1, NetRowsArgs a, hipStream_t s);

@@ -25,27 +25,9 @@
 #include <vector>
 
 #include "cold_internal.h"
+#include "gather_tile.h"
 
 namespace cold {
-
-// last q with req_off[q] <= r, clamped to [0, Q-1]
-__device__ __forceinline__ int64_t request_of_row(const int32_t *req_off, int64_t Q, int64_t r) {
-  int64_t lo = 0, hi = Q;  // invariant: answer in [lo, hi)
-  while (hi - lo > 1) {
-    int64_t mid = (lo + hi) >> 1;
-    if ((int64_t)req_off[mid] <= r) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// Eq. 3: identity on [-1, 1], sign(x) (1 + ln|x|) outside, branch-free.  The
-// natural log comes from the hardware log2 (relative error near 2^-22),
-// far below the half-precision rounding that follows it.
-__device__ __forceinline__ float linear_log(float x) {
-  const float ax = fabsf(x);
-  const float l = __logf(ax) + 1.0f;   // used only when |x| > 1
-  return ax > 1.0f ? copysignf(l, x) : x;
-}
 
 __global__ void clear_flag_kernel(int32_t *err) { *err = 0; }
 
@@ -863,10 +845,6 @@ static int resident_blocks(const void *kernel, size_t shmem) {
 // rounding.  A row's result does not depend on the other rows of its tile,
 // and every batch size of a model takes the same form, so a score does not
 // depend on the batch it comes in.
-constexpr int kFullMaxM = 64;
-constexpr int kFullMaxH = 16;
-constexpr int kFullTileM = 48;   // the one-wave-per-tile form up to this many groups
-
 bool gather_full_shape(int32_t M, int32_t H, int32_t row_bytes, int32_t n_seq) {
   return n_seq == 0 && M > 0 && M <= kFullMaxM && H > 0 && H <= kFullMaxH && row_bytes == 32;
 }

@@ -1,0 +1,33 @@
+// gather_tile.h -- device pieces shared by the gathers (gather.hip) and the
+// fp32 model's one-kernel path (net_f32.hip).
+#pragma once
+
+#include "cold_internal.h"
+
+namespace cold {
+
+// last q with req_off[q] <= r, clamped to [0, Q-1]
+__device__ __forceinline__ int64_t request_of_row(const int32_t *req_off, int64_t Q, int64_t r) {
+  int64_t lo = 0, hi = Q;  // invariant: answer in [lo, hi)
+  while (hi - lo > 1) {
+    int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)req_off[mid] <= r) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// Eq. 3: identity on [-1, 1], sign(x) (1 + ln|x|) outside, branch-free.  The
+// natural log comes from the hardware log2 (relative error near 2^-22),
+// far below the half-precision rounding that follows it.
+__device__ __forceinline__ float linear_log(float x) {
+  const float ax = fabsf(x);
+  const float l = __logf(ax) + 1.0f;   // used only when |x| > 1
+  return ax > 1.0f ? copysignf(l, x) : x;
+}
+
+// shape limits of the register-resident gathers
+constexpr int kFullMaxM = 64;
+constexpr int kFullMaxH = 16;
+constexpr int kFullTileM = 48;   // the one-wave-per-tile form up to this many groups
+
+}  // namespace cold

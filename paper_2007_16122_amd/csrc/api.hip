@@ -21,6 +21,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct ArenaLayout {
   size_t tables, rows, magic, pairs, w1, b1, w2, b2, w1t, w2t, w1p, w2p, w1f, w2f;
+  size_t wl, wl_unscale;   // the literal SE layer's packed weights
   std::vector<size_t> w, b;
   std::vector<size_t> wf;   // fragment-major copies of the row-tile network's layers (net_first)
   size_t total;
@@ -84,6 +85,12 @@ int hip_fail(cold_model *m, hipError_t e, const char *what) {
 // SE operands of the register-resident gather (squeeze form; its shape limits)
 bool full_gather_model(const cold_model &m) {
   return !m.literal_se && gather_full_shape(m.M, m.H, m.d * m.es, m.desc.n_seq);
+}
+
+// The literal SE form on the half-precision matrix cores: the gathered rows
+// must be exact in the storage type (no pooled sequences).
+bool literal_split(const cold_model &m) {
+  return m.literal_se && m.dtype != kF32 && m.desc.n_seq == 0;
 }
 
 bool topk_split(const cold_model &m) {
@@ -154,6 +161,8 @@ ArenaLayout arena_layout(const cold_model &m) {
   a.w2p = take(sizeof(float) * n2);
   a.w1f = take(full_gather_model(m) ? sizeof(float) * kSeFullFloats : 0);
   a.w2f = take(full_gather_model(m) ? sizeof(float) * kSeFullFloats : 0);
+  a.wl = take(literal_split(m) ? m.es * literal_packed_elems(m.M, m.D_in) : 0);
+  a.wl_unscale = take(literal_split(m) ? sizeof(float) * literal_features(m.M) : 0);
   const int L = m.desc.n_layers;
   for (int l = 0; l < L; ++l) {
     a.w.push_back(take((size_t)m.es * m.widths[l] * m.widths[l + 1]));
@@ -178,7 +187,7 @@ WorkLayout work_layout(const cold_model &m, int64_t R, int64_t Q) {
   w.Uh = take((size_t)m.es * Q * m.desc.n_user * m.d);
   w.urow = take(sizeof(int32_t) * (size_t)Q * (m.desc.n_user > 0 ? m.desc.n_user : 1));
   w.X = take((size_t)m.es * R * m.D_in);
-  w.E = take(m.literal_se ? sizeof(float) * (size_t)R * m.D_in : 0);
+  w.E = take(m.literal_se && !literal_split(m) ? sizeof(float) * (size_t)R * m.D_in : 0);
   w.actA = take((size_t)m.es * R * m.max_hidden);
   w.actB = take((size_t)m.es * R * m.max_hidden);
   w.sbuf = take(sbuf ? sizeof(float) * (size_t)R * m.M : 0);
@@ -431,6 +440,11 @@ int cold_load_weights(cold_model *m, const cold_weights *w, void *arena, size_t 
                                reinterpret_cast<float *>(A + al.w2t), m->M, m->H, s);
     if (e != hipSuccess) return hip_fail(m, e, "cold_load_weights: transpose");
   }
+  if (literal_split(*m)) {
+    hipError_t e = launch_pack_literal(m->dtype, reinterpret_cast<const float *>(A + al.w1), m->M, m->D_in,
+                                       A + al.wl, reinterpret_cast<float *>(A + al.wl_unscale), s);
+    if (e != hipSuccess) return hip_fail(m, e, "cold_load_weights: SE pack");
+  }
   if (topk_split(*m)) {
     hipError_t e = launch_pack_se_rows(reinterpret_cast<const float *>(A + al.w1),
                                        reinterpret_cast<const float *>(A + al.w2), m->M, m->H,
@@ -572,7 +586,40 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
     if ((e = launch_user_pool(m->dtype, m->hashed, g, s)) != hipSuccess)
       return hip_fail(m, e, "user_pool launch");
   }
-  if (m->literal_se) {
+  const int l0 = net_first(*m);
+  const bool net_rows = l0 >= 0 && net_rows_chosen(R);
+  // the reweighting of a literal-SE model's rows left to the network kernel
+  bool weigh_later = false;
+  if (literal_split(*m)) {
+    // Eq. 2 as printed: the rows as they are, the weights from them, the
+    // reweighting in place or, in large batches without a mask, as the
+    // network reads the rows
+    float *sb = importance ? importance : reinterpret_cast<float *>(W + wl.sbuf);
+    g.z_out = nullptr;
+    if ((e = marks.mark("gather_raw")) != hipSuccess) return hip_fail(m, e, "profile event");
+    if ((e = launch_gather_se(m->dtype, kSqueezeRaw, false, m->hashed, g, s)) != hipSuccess)
+      return hip_fail(m, e, "gather (raw) launch");
+    weigh_later = net_rows && l0 == 0 && !topk && !x_out;
+    const bool weighed = !weigh_later && !topk && se_literal_applies(m->D_in);   // by the SE layer's kernel
+    if ((e = marks.mark("se_literal")) != hipSuccess) return hip_fail(m, e, "profile event");
+    if ((e = launch_se_literal(m->dtype, W + wl.X, A + al.wl, reinterpret_cast<const float *>(A + al.wl_unscale),
+                               g.b1, sb, R, m->M, m->D_in, m->d, weighed, D.linear_log, s)) != hipSuccess)
+      return hip_fail(m, e, "SE layer launch");
+    uint8_t *mask = topk ? W + wl.mask : nullptr;
+    if (topk) {
+      if ((e = marks.mark("group_mask")) != hipSuccess) return hip_fail(m, e, "profile event");
+      if ((e = launch_group_mask(sb, b->req_off, Q, R, m->M, D.topk_k, reinterpret_cast<float *>(W + wl.partial),
+                                 kMaskParts, mask, group_mask, s)) != hipSuccess)
+        return hip_fail(m, e, "group_mask launch");
+    }
+    if (!weigh_later && !weighed) {
+      if ((e = marks.mark("apply")) != hipSuccess) return hip_fail(m, e, "profile event");
+      if ((e = launch_apply_weights(m->dtype, D.linear_log, W + wl.X, sb, mask, b->req_off, Q, R, m->M, m->d,
+                                    s)) != hipSuccess)
+        return hip_fail(m, e, "apply launch");
+    }
+    g.s_buf = sb;
+  } else if (m->literal_se) {
     // Eq. 2 as printed: the concatenated embedding (fp32), one dense layer
     // with a sigmoid to the M weights, then the reweighting pass
     float *sb = importance ? importance : reinterpret_cast<float *>(W + wl.sbuf);
@@ -685,8 +732,6 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
                                                m->widths[n_separate - 1]);
   const void *in = W + wl.X;
   unsigned char *bufs[2] = {W + wl.actA, W + wl.actB};
-  const int l0 = net_first(*m);
-  const bool net_rows = l0 >= 0 && net_rows_chosen(R);
   TailArgs tail{};
   if (fuse_tail)
     tail = {A + al.w[L - 3], reinterpret_cast<const float *>(A + al.b[L - 3]), A + al.w[L - 2],
@@ -713,6 +758,7 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
     auto bias = [&](int i) { return reinterpret_cast<const float *>(A + al.b[l0 + i]); };
     NetRowsArgs na{};
     na.x = in;
+    if (weigh_later) na.weights = g.s_buf, na.d = m->d, na.linear_log = D.linear_log;
     na.w0 = A + al.wf[0]; na.b0 = bias(0);
     if (nl == 3) na.w1 = A + al.wf[1], na.b1 = bias(1);
     na.w2 = A + al.wf[nl - 1]; na.b2 = bias(nl - 1);

@@ -191,8 +191,9 @@ struct GatherArgs {
 // kApplyWeights: reweight with s_buf (groups outside `mask`, when given,
 // read nothing and get weight 0); kRawOut: the concatenated embedding in
 // fp32 to X, for an SE computed elsewhere
-// kSqueezeRaw: the squeeze to z_out [R][M] and the gathered rows, exact in the
-// storage type, to X, for se_rows and apply_weights (models without sequences)
+// kSqueezeRaw: the squeeze to z_out [R][M] (when not null) and the gathered
+// rows, exact in the storage type, to X, for an SE of its own and
+// apply_weights (models without sequences)
 enum GatherMode { kFull = 0, kWeightsOnly = 1, kApplyWeights = 2, kRawOut = 3, kSqueezeRaw = 4 };
 
 // launchers (return hipError_t of the launch)
@@ -355,6 +356,10 @@ hipError_t launch_dense_tail(int dtype, const void *x, const void *w, const floa
 // the whole network over 64-row tiles in one kernel (net_rows.hip)
 struct NetRowsArgs {
   const void *x;          // [R][K0]
+  // when not null: [R][K0 / d] weights of x's groups of d values (applied, with
+  // linear_log, as the rows are read)
+  const float *weights;
+  int32_t d, linear_log;
   const void *w0, *w1, *w2;   // fragment-major; w1 only with three separate layers
   const float *b0, *b1, *b2;
   TailArgs tail;
@@ -362,6 +367,18 @@ struct NetRowsArgs {
   int64_t R, tiles;
   int32_t K0;
 };
+// the literal SE layer on exact gathered rows X [R][K] (half precision):
+// s [R][M] = sigmoid(W X^T + b), W packed by launch_pack_literal
+size_t literal_packed_elems(int32_t M, int32_t K);
+int32_t literal_features(int32_t M);
+hipError_t launch_pack_literal(int dtype, const float *w, int32_t M, int32_t K, void *wp, float *unscale,
+                               hipStream_t s);
+// (K = M d; with apply, for K that se_literal_applies to, X becomes the
+// network input in place: weighted, linear_log when ll, rounded once)
+bool se_literal_applies(int32_t K);
+hipError_t launch_se_literal(int dtype, void *x, const void *wp, const float *unscale, const float *b,
+                             float *s_out, int64_t R, int32_t M, int32_t K, int32_t d, bool apply, bool ll,
+                             hipStream_t s);
 // a small fp32 model (squeeze-form SE, two hidden layers of at most 64) in one
 // kernel, from the ids to the CTR (net_f32.hip); g as for the gathers, X
 // written only when g.X is not null

@@ -377,6 +377,8 @@ __global__ __launch_bounds__(kGatherThreads, CPT <= 8 ? 4 : 2) void gather_se_ke
   if constexpr (MODE == kFull || MODE == kWeightsOnly || MODE == kSqueezeRaw) {
     int t = tf, c = cf;
     asm volatile("" : "+v"(t), "+v"(c));   // recomputed per phase, not kept live
+    const bool squeeze = MODE != kSqueezeRaw || a.z_out != nullptr;   // the same for every wave
+    if (squeeze)
 #pragma unroll
     for (int j = 0; j < CPT; ++j, advance(t, c)) {
       const int g = c >> lcpg, p = c & (CPG - 1);
@@ -400,7 +402,7 @@ __global__ __launch_bounds__(kGatherThreads, CPT <= 8 ? 4 : 2) void gather_se_ke
     if constexpr (MODE == kSqueezeRaw) {
       // the squeeze [R][M] and the gathered rows, exact in the storage type,
       // into the network input's place, for the separate SE and apply passes
-      for (int it = ln; it < Tw * M; it += 64) {
+      if (a.z_out) for (int it = ln; it < Tw * M; it += 64) {
         const int t = fast_div(it, a.mg_m), g = it - t * M;
         if (r0 + t < R) a.z_out[r0 * M + it] = z[t * Mp + g];
       }
@@ -1729,7 +1731,7 @@ template <typename TS>
 static hipError_t gather_se_dt(int mode, bool ll, bool hashed, const GatherArgs &a, hipStream_t s) {
   if (mode == kWeightsOnly) return gather_se_t<TS, kWeightsOnly, false>(hashed, a, s);
   if (mode == kSqueezeRaw) {
-    if (a.n_seq > 0 || !a.z_out) return hipErrorInvalidValue;   // pooled sums are not exact in TS
+    if (a.n_seq > 0) return hipErrorInvalidValue;   // pooled sums are not exact in TS
     return gather_se_t<TS, kSqueezeRaw, false>(hashed, a, s);
   }
   if (mode == kRawOut) return gather_se_t<TS, kRawOut, false>(hashed, a, s);

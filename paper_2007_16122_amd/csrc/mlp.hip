@@ -571,7 +571,7 @@ __global__ __launch_bounds__(128 * WN, MINB) void dense_tail_kernel(
     // lr % (PR/2) of the tile
     tail_rows<TS, PR, JB, true, !W_EARLY>(smem, smem, tw, t, s_wh, scores,
                                 [&](int lr) { return r0 + (lr / (PR / 2)) * (BR / 2) + p * (PR / 2) + lr % (PR / 2); },
-                                R, tid, lane, wave);
+                                R, tid, lane, wave, []() {});
     if (p + 1 < NP) __syncthreads();   // the next pass overwrites the tail's tiles
   }
 }

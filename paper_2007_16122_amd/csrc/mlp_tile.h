@@ -246,11 +246,13 @@ template <typename TS> struct TailWeights {
 // features 16 fb + 4 q + e of row c; its four products are added in e order,
 // the four quarters by two shuffles, the four blocks in order from LDS.
 // LATE: the biases are loaded here (the caller's registers are full before).
-template <typename TS, int PR, int JB, bool ALIAS, bool LATE, typename RowOf>
+// mid() runs once the first layer's weights are dead.
+template <typename TS, int PR, int JB, bool ALIAS, bool LATE, typename RowOf, typename Mid>
 __device__ __forceinline__ void tail_rows(unsigned char *hl, unsigned char *out,
                                           TailWeights<TS> &tw, const TailArgs &t,
                                           const float *s_wh, float *__restrict__ scores,
-                                          const RowOf &row_of, int64_t R, int tid, int lane, int wave) {
+                                          const RowOf &row_of, int64_t R, int tid, int lane, int wave,
+                                          const Mid &mid) {
   constexpr int KS1 = TailWeights<TS>::KS1, KS2 = TailWeights<TS>::KS2, N2 = kTailN2, S1 = kTailS1;
   TS *s_h1 = reinterpret_cast<TS *>(out);
   float *s_h2 = reinterpret_cast<float *>(out + 2 * PR * S1 * 2);
@@ -263,6 +265,7 @@ __device__ __forceinline__ void tail_rows(unsigned char *hl, unsigned char *out,
   tail_mma<TS, KS1, 2, JB, true>(in0, PR * kTailHRow, tw.w1, (wave / 4) * JB, lane, a1);
   if (ALIAS) __syncthreads();   // the pairs are dead once every wave has its sums
   if constexpr (LATE) tw.load_bias(t, wave, lane);
+  mid();
   tail_store_ext<TS, 2, JB>(a1, tw.b1, s_h1, S1, PR * S1, 2 * (wave % 4), (wave / 4) * JB, lane);
   __syncthreads();
   auto in1 = [&](int row, int c) { return s_h1 + row * S1 + c * 8; };

@@ -23,6 +23,7 @@
 //   Every sum runs over the same 32-deep K blocks in the same order as the
 // layer-by-layer path, so a score does not depend on which one computed it.
 #include "cold_internal.h"
+#include "gather_tile.h"
 #include "mlp_tile.h"
 
 namespace cold {
@@ -181,7 +182,7 @@ __device__ __forceinline__ void store_act(const f32x4 (&acc)[NI][RJ], unsigned c
 
 }  // namespace
 
-template <typename TS, int N0, int N1, int NX, bool ODD>
+template <typename TS, int N0, int N1, int NX, bool ODD, bool WEIGH>
 __global__ __launch_bounds__(64 * kWaves, 1) void net_rows_kernel(NetRowsArgs a) {
   typedef typename Mfma<TS>::frag frag;
   constexpr int NI0 = N0 / kWaves / 16;                 // first layer: 16-wide blocks of a wave
@@ -216,15 +217,19 @@ __global__ __launch_bounds__(64 * kWaves, 1) void net_rows_kernel(NetRowsArgs a)
     put(a.tail.bh, BOH + 2 * kTailN2, a.tail.n_out);
   }
   // a tile's input rows in registers: thread t holds chunks t % 8 + 8 u of
-  // row t / 8 (u < NX covers K0; loads past the row's end repeat its last chunk)
+  // row t / 8 (u < NX covers K0; loads past the row's end repeat its last
+  // chunk); WEIGH: and the weight of each chunk's group
   uint4 xv[NX];
+  float sv[WEIGH ? NX : 1];
+  const int lcpg = WEIGH ? __builtin_ctz(a.d / 8) : 0, groups = WEIGH ? a.K0 / a.d : 0;
   auto load_x = [&](int64_t tile, int tid) {
-    const int64_t r = tile * kRows + (tid >> 3);
-    const TS *xp = X + (r < a.R ? r : a.R - 1) * K0;
+    const int64_t rt = tile * kRows + (tid >> 3), r = rt < a.R ? rt : a.R - 1;
+    const TS *xp = X + r * a.K0;
 #pragma unroll
     for (int u = 0; u < NX; ++u) {
       const int ch = u * 8 + (tid & 7);
       xv[u] = *reinterpret_cast<const uint4 *>(xp + (ch < nch ? ch : nch - 1) * 8);
+      if constexpr (WEIGH) sv[u] = a.weights[r * groups + ((ch < nch ? ch : nch - 1) >> lcpg)];
     }
   };
   // and the first layer's first weight fragments
@@ -252,6 +257,16 @@ __global__ __launch_bounds__(64 * kWaves, 1) void net_rows_kernel(NetRowsArgs a)
 #pragma unroll
     for (int u = 0; u < NX; ++u) {
       const int ch = u * 8 + (tid & 7);
+      if constexpr (WEIGH) {
+        float v[8];
+        Elem<TS>::unpack(xv[u], v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = sv[u] * v[e];
+        if (a.linear_log)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = linear_log(v[e]);
+        xv[u] = Elem<TS>::pack(v);
+      }
       *reinterpret_cast<uint4 *>(smem + row_slot<XROW>(tid >> 3, ch)) =
           ch < nch ? xv[u] : make_uint4(0, 0, 0, 0);
     }
@@ -316,10 +331,9 @@ __global__ __launch_bounds__(64 * kWaves, 1) void net_rows_kernel(NetRowsArgs a)
         tail_put_pair<TS, kRows>(acc2[i][j], hl, (wave * NI2 + i) * 16 + dn, j * 16 + c);
     lds_barrier();
     phase_end();
-    load_w0(w0);   // and its first weights
     tw.bias_from(s_b + BO3, s_b + BO4, wave, lane);
     tail_rows<TS, kRows, 2, false, false>(hl, smem, tw, a.tail, s_b + BOH, a.scores, [&](int lr) { return r0 + lr; },
-                                          a.R, tid, lane, wave);
+                                          a.R, tid, lane, wave, [&]() { load_w0(w0); });
     lds_barrier();   // the next tile's rows take the place of the tail's
   }
 }
@@ -343,32 +357,35 @@ bool net_rows_chosen(int64_t R) {
   return (R + kRows - 1) / kRows * 8 >= 3 * cus;
 }
 
-template <typename TS, int N0, int N1, int NX>
+template <typename TS, int N0, int N1, int NX, bool WEIGH>
 static void net_rows_k(const NetRowsArgs &a, unsigned grid, hipStream_t s) {
   if (((a.K0 + 31) / 32) % 2)
-    hipLaunchKernelGGL((net_rows_kernel<TS, N0, N1, NX, true>), dim3(grid), dim3(64 * kWaves), 0, s, a);
+    hipLaunchKernelGGL((net_rows_kernel<TS, N0, N1, NX, true, WEIGH>), dim3(grid), dim3(64 * kWaves), 0, s, a);
   else
-    hipLaunchKernelGGL((net_rows_kernel<TS, N0, N1, NX, false>), dim3(grid), dim3(64 * kWaves), 0, s, a);
+    hipLaunchKernelGGL((net_rows_kernel<TS, N0, N1, NX, false, WEIGH>), dim3(grid), dim3(64 * kWaves), 0, s, a);
 }
 
-template <typename TS>
+template <typename TS, bool WEIGH>
 static hipError_t net_rows_t(int32_t n0, const NetRowsArgs &a, hipStream_t s) {
   const int cus = device_cus() > 0 ? device_cus() : 256;
   const unsigned grid = (unsigned)(a.tiles < cus ? a.tiles : cus);
-  if (n0 == 1024 && a.K0 <= 768) net_rows_k<TS, 1024, 512, 12>(a, grid, s);
-  else if (n0 == 1024) net_rows_k<TS, 1024, 512, 16>(a, grid, s);
-  else if (a.K0 <= 768) net_rows_k<TS, 512, 0, 12>(a, grid, s);
-  else net_rows_k<TS, 512, 0, 16>(a, grid, s);
+  if (n0 == 1024 && a.K0 <= 768) net_rows_k<TS, 1024, 512, 12, WEIGH>(a, grid, s);
+  else if (n0 == 1024) net_rows_k<TS, 1024, 512, 16, WEIGH>(a, grid, s);
+  else if (a.K0 <= 768) net_rows_k<TS, 512, 0, 12, WEIGH>(a, grid, s);
+  else net_rows_k<TS, 512, 0, 16, WEIGH>(a, grid, s);
   return hipGetLastError();
 }
 
 hipError_t launch_net_rows(int dtype, int32_t n0, int32_t n1, NetRowsArgs a, hipStream_t s) {
   if (a.R <= 0) return hipSuccess;
   if (dtype == kF32 || a.K0 <= 64 || a.K0 > kNetRowsMaxK || a.K0 % 8 != 0 ||
-      (n0 == 1024 ? n1 != 512 : n0 != 512 || n1 != 0))
+      (n0 == 1024 ? n1 != 512 : n0 != 512 || n1 != 0) ||
+      (a.weights && (a.d < 8 || (a.d & (a.d - 1)) || a.K0 % a.d)))
     return hipErrorNotSupported;
   a.tiles = (a.R + kRows - 1) / kRows;
-  return dtype == kBF16 ? net_rows_t<__bf16>(n0, a, s) : net_rows_t<_Float16>(n0, a, s);
+  if (a.weights)
+    return dtype == kBF16 ? net_rows_t<__bf16, true>(n0, a, s) : net_rows_t<_Float16, true>(n0, a, s);
+  return dtype == kBF16 ? net_rows_t<__bf16, false>(n0, a, s) : net_rows_t<_Float16, false>(n0, a, s);
 }
 
 }  // namespace cold

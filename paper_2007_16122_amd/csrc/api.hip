@@ -555,6 +555,8 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
   g.urow = reinterpret_cast<int32_t *>(W + wl.urow);
   g.X = W + wl.X;
   g.rows_out = rows_out;
+  g.hashed = m->hashed;
+  g.linear_log = D.linear_log;
   g.err = reinterpret_cast<int32_t *>(W + wl.err);
 
   hipError_t e;
@@ -576,7 +578,7 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
     auto W_ = [&](int l) { return reinterpret_cast<const float *>(A + al.w[l]); };
     auto B_ = [&](int l) { return reinterpret_cast<const float *>(A + al.b[l]); };
     const NetF32Args n{W_(0), B_(0), W_(1), B_(1), W_(2), B_(2), scores,
-                       m->widths[1], m->widths[2], m->widths[3], m->hashed, D.linear_log};
+                       m->widths[1], m->widths[2], m->widths[3]};
     if ((e = marks.mark("net_f32")) != hipSuccess) return hip_fail(m, e, "profile event");
     if ((e = launch_net_f32(g, n, s)) != hipSuccess) return hip_fail(m, e, "network launch");
     return finish(m, marks, g.err, validate, s);

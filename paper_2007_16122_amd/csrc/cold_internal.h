@@ -185,6 +185,7 @@ struct GatherArgs {
   const uint8_t *mask;            // [Q][M] kept groups (apply mode)
   int32_t *rows_out;              // [M][R] or null
   int32_t *err;                   // error bits
+  int32_t hashed, linear_log;     // of the model, for kernels without them as template parameters
 };
 
 // kFull: SE and reweighting in one pass; kWeightsOnly: SE weights to s_buf;
@@ -199,14 +200,17 @@ enum GatherMode { kFull = 0, kWeightsOnly = 1, kApplyWeights = 2, kRawOut = 3, k
 // launchers (return hipError_t of the launch)
 bool user_pool_needed(int dtype, const GatherArgs &a);
 hipError_t launch_user_pool(int dtype, bool hashed, const GatherArgs &a, hipStream_t s);
-// the register-resident kFull gather (M <= 48, H <= 16, 32-byte group rows,
-// no sequences; needs the packed SE operands, and the pooling pass where
-// user_pool_needed says so)
+// the register-resident kFull gathers (at most 64 groups, 16 hidden SE units
+// and 16- or 32-byte group rows; they need the packed SE operands, and the pooling
+// pass where user_pool_needed says so)
 constexpr int kSeFullFloats = 4 * 64 * 4;   // floats of each packed operand
 bool gather_full_shape(int32_t M, int32_t H, int32_t row_bytes, int32_t n_seq);
 bool gather_full_supported(int dtype, const GatherArgs &a);
 hipError_t launch_gather_full(int dtype, bool linear_log, bool hashed, const GatherArgs &a,
                               hipStream_t s);
+hipError_t launch_gather_split(int dtype, const GatherArgs &a, hipStream_t s);
+// workgroups of a kernel resident on the current device (cached)
+int resident_blocks(const void *kernel, int threads, size_t shmem);
 hipError_t launch_pack_se_full(const float *w1, const float *w2, int32_t M, int32_t H, float *w1f,
                                float *w2f, hipStream_t s);
 hipError_t launch_gather_se(int dtype, int mode, bool linear_log, bool hashed,
@@ -386,7 +390,6 @@ struct NetF32Args {
   const float *w1, *b1, *w2, *b2, *wh, *bh;
   float *scores;
   int32_t n1, n2, n_out;
-  int32_t hashed, linear_log;
 };
 bool net_f32_shape(int32_t M, int32_t H, int32_t row_bytes, int32_t n_seq, const int32_t *widths,
                    int32_t n_layers);

@@ -25,6 +25,20 @@ __device__ __forceinline__ float linear_log(float x) {
   return ax > 1.0f ? copysignf(l, x) : x;
 }
 
+// Eq. 3 on a lane's N values. It leaves |x| <= 1 as it is, so the logarithms
+// (a quarter-rate instruction and six more each) run only where a lane of
+// the wave holds a larger value: a pooled sequence, hardly ever an embedding.
+template <int N>
+__device__ __forceinline__ void linear_log_all(float (&v)[N]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) m = fmaxf(m, fabsf(v[e]));
+  if (__any(m > 1.0f)) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = linear_log(v[e]);
+  }
+}
+
 // shape limits of the register-resident gathers
 constexpr int kFullMaxM = 64;
 constexpr int kFullMaxH = 16;

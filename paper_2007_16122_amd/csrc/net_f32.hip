@@ -116,10 +116,10 @@ __global__ __launch_bounds__(256) void net_f32_kernel(GatherArgs a, NetF32Args n
       const int64_t at = f < 0 ? (int64_t)g * Q + rq : (int64_t)fc * R + rr;
       id[u] = uid[u] = 0;
       if (g < M) {
-        id[u] = n.hashed ? static_cast<const uint64_t *>(base)[at] : static_cast<const uint32_t *>(base)[at];
+        id[u] = a.hashed ? static_cast<const uint64_t *>(base)[at] : static_cast<const uint32_t *>(base)[at];
         if (is_cross && gpu_cross) {
           const int64_t ua = (int64_t)(pair[u] & 0xFFFF) * Q + rq;
-          uid[u] = n.hashed ? static_cast<const uint64_t *>(a.user_ids)[ua]
+          uid[u] = a.hashed ? static_cast<const uint64_t *>(a.user_ids)[ua]
                             : static_cast<const uint32_t *>(a.user_ids)[ua];
         }
       }
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void net_f32_kernel(GatherArgs a, NetF32Args n
       const uint64_t key = built ? mix64(uid[u]) ^ id[u] : id[u];
       const uint64_t salt = (uint64_t)(g + 1) * 0x9e3779b97f4a7c15ull;
       int32_t row = (int32_t)(uint32_t)id[u];
-      if (n.hashed || built) row = (int32_t)mod_barrett(mix64(key ^ salt), (uint64_t)nrows[u], magic[u]);
+      if (a.hashed || built) row = (int32_t)mod_barrett(mix64(key ^ salt), (uint64_t)nrows[u], magic[u]);
       const bool ok = row >= 0 && row < nrows[u];
       if (g < M && !ok) atomicOr(a.err, 1);
       if (a.rows_out && g < M && row_ok) a.rows_out[(int64_t)g * R + r] = ok ? row : -1;
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256) void net_f32_kernel(GatherArgs a, NetF32Args n
       const int g = tg + 16 * u;
       const float sw = s_s[trow * kStride + g];
       f4 x0 = sw * e0[u], x1 = sw * e1[u];
-      if (n.linear_log) {
+      if (a.linear_log) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           x0[e] = linear_log(x0[e]);
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void net_f32_kernel(GatherArgs a, NetF32Args n
 }  // namespace
 
 bool net_f32_shape(int32_t M, int32_t H, int32_t row_bytes, int32_t n_seq, const int32_t *w, int32_t L) {
-  return gather_full_shape(M, H, row_bytes, n_seq) && L == 3 && w[1] % 4 == 0 && w[1] <= 64 &&
+  return gather_full_shape(M, H, row_bytes, n_seq) && row_bytes == 32 && n_seq == 0 && L == 3 && w[1] % 4 == 0 && w[1] <= 64 &&
          w[2] <= 64 && (w[3] == 1 || w[3] == 2);
 }
 

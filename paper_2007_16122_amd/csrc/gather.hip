@@ -824,8 +824,8 @@ int resident_blocks(const void *kernel, int threads, size_t shmem) {
 // ------------------------------------------------------------- gather_full
 // Gather, squeeze, SE and reweighting of a row tile in registers (Section
 // 3.2: Eq. 2 read as squeeze -> FC -> ReLU -> FC -> sigmoid, Eq. 3 when LL),
-// for models with at most 64 groups, at most 16 hidden SE units, 32-byte
-// group rows and no sequence groups.  A tile is 16 rows; lane l = 16 q + c
+// for models with at most 64 groups, at most 16 hidden SE units and 16- or
+// 32-byte group rows; this form: 32 bytes and no sequence groups.  A tile is 16 rows; lane l = 16 q + c
 // of a wave owns row c and groups g = 4 k + q of its slots k: it loads their
 // ids and both 16-byte chunks of each group row itself, so a group's squeeze
 // is a sum inside one lane, and the lanes' squeeze values are already the B
@@ -838,23 +838,21 @@ int resident_blocks(const void *kernel, int threads, size_t shmem) {
 // operand order at load time and staged in LDS.  The users' rows come from
 // the pooling pass (storage type, one per request), or, for few requests,
 // are resolved into LDS by every workgroup.
-//   Up to 48 groups, one wave takes a whole tile (12 slots per lane, held in
-// registers from the gather to the store).  Above that, a workgroup takes a
-// tile with one wave per 16 groups (4 slots per lane); each wave forms
-// layer 1's sum over its own slots (wave 0's from b1), the parts are added
-// in wave order through LDS, and wave w forms layer 2's block gb = w.
+//   Up to 48 groups of 32 bytes, one wave takes a whole tile (12 slots per
+// lane, held in registers from the gather to the store). Other shapes, and
+// middle batches, take a tile with one wave per 16 groups (gather_split.hip).
 //   Products and sums are fp32; the squeeze and the SE sums run in another
 // order than the general gather's index order, which only moves fp32
 // rounding.  A row's result does not depend on the other rows of its tile,
-// and every batch size of a model takes the same form, so a score does not
-// depend on the batch it comes in.
+// and the forms that batches of one model choose between (launch_gather_full)
+// give the same bits, so a score does not depend on the batch it comes in.
 bool gather_full_shape(int32_t M, int32_t H, int32_t row_bytes, int32_t n_seq) {
   return n_seq >= 0 && M > 0 && M <= kFullMaxM && H > 0 && H <= kFullMaxH &&
          (row_bytes == 16 || row_bytes == 32);
 }
 
-// every batch size of a supported model takes this kernel, so that a row's
-// score does not depend on the batch it comes in
+// by the model alone: every batch size of it takes these gathers, so that a
+// row's score does not depend on the batch it comes in
 bool gather_full_supported(int dtype, const GatherArgs &a) {
   const int es = dtype == kF32 ? 4 : 2;
   return gather_full_shape(a.M, a.H, a.d * es, a.n_seq) && a.w1f != nullptr && a.w2f != nullptr;

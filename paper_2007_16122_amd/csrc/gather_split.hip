@@ -4,13 +4,14 @@
 //
 // Lane l = 16 q + c of wave w owns row c and the groups 16 w + 4 j + q of its
 // four slots, as in gather_full_kernel: the squeeze of a group is a sum inside
-// one lane and already the B operand of the SE's fp32 MFMAs. Each wave forms
-// layer 1 over its own slots (wave 0's from b1), the parts are added in wave
-// order through LDS (double-buffered by tile parity, one barrier a tile), and
-// wave w forms layer 2's block w, whose weights land in the lanes that hold
-// the values. A pooled group takes its squeeze from the pooling pass and its
-// fp32 values from there when it is weighted (one cache line for all rows of
-// a request). The next tile's ids load while this tile's rows do.
+// one lane. The squeeze of the tile goes to LDS (double-buffered by tile parity,
+// one barrier a tile); every wave then forms the whole of layer 1 on the fp32
+// MFMAs, its steps in the one-wave form's order, and wave w forms layer 2's
+// block w, whose weights land in the lanes that hold the values. So both forms
+// give the same bits and the batch may choose between them. A pooled group
+// takes its squeeze from the pooling pass and its fp32 values from there when
+// it is weighted (one cache line for all rows of a request). The next tile's
+// ids load while this tile's rows do.
 //   Bound by the random row reads: the 1.28 M-row workload's 64 groups move
 // 8.8 GB at 5.0 TB/s, the rate of a large copy. Against the general gather
 // (stage events): 64,000 rows of 54 groups, 6 of them pooled, with linear_log

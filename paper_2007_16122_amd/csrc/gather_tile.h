@@ -1,5 +1,7 @@
-// gather_tile.h -- device pieces shared by the gathers (gather.hip) and the
-// fp32 model's one-kernel path (net_f32.hip).
+// gather_tile.h -- device pieces shared by the gathers (gather.hip,
+// gather_split.hip), the fp32 model's one-kernel path (net_f32.hip), the
+// network over row tiles (net_rows.hip) and the literal SE layer
+// (se_literal.hip).
 #pragma once
 
 #include "cold_internal.h"

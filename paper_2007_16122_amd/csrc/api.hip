@@ -604,7 +604,7 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
     weigh_later = net_rows && l0 == 0 && !topk && !x_out;
     const bool weighed = !weigh_later && !topk && se_literal_applies(m->D_in);   // by the SE layer's kernel
     if ((e = marks.mark("se_literal")) != hipSuccess) return hip_fail(m, e, "profile event");
-    if ((e = launch_se_literal(m->dtype, W + wl.X, A + al.wl, reinterpret_cast<const float *>(A + al.wl_unscale),
+    if ((e = launch_se_literal(m->dtype, W + wl.X, g.w1, A + al.wl, reinterpret_cast<const float *>(A + al.wl_unscale),
                                g.b1, sb, R, m->M, m->D_in, m->d, weighed, D.linear_log, s)) != hipSuccess)
       return hip_fail(m, e, "SE layer launch");
     uint8_t *mask = topk ? W + wl.mask : nullptr;

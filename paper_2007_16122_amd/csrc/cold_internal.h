@@ -372,7 +372,7 @@ struct NetRowsArgs {
   int32_t K0;
 };
 // the literal SE layer on exact gathered rows X [R][K] (half precision):
-// s [R][M] = sigmoid(W X^T + b), W packed by launch_pack_literal
+// s [R][M] = sigmoid(W X^T + b), W as it is (w) and packed by launch_pack_literal (wp)
 size_t literal_packed_elems(int32_t M, int32_t K);
 int32_t literal_features(int32_t M);
 hipError_t launch_pack_literal(int dtype, const float *w, int32_t M, int32_t K, void *wp, float *unscale,
@@ -380,7 +380,7 @@ hipError_t launch_pack_literal(int dtype, const float *w, int32_t M, int32_t K, 
 // (K = M d; with apply, for K that se_literal_applies to, X becomes the
 // network input in place: weighted, linear_log when ll, rounded once)
 bool se_literal_applies(int32_t K);
-hipError_t launch_se_literal(int dtype, void *x, const void *wp, const float *unscale, const float *b,
+hipError_t launch_se_literal(int dtype, void *x, const float *w, const void *wp, const float *unscale, const float *b,
                              float *s_out, int64_t R, int32_t M, int32_t K, int32_t d, bool apply, bool ll,
                              hipStream_t s);
 // a small fp32 model (squeeze-form SE, two hidden layers of at most 64) in one

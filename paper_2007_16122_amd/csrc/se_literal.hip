@@ -73,6 +73,22 @@ __global__ __launch_bounds__(256) void pack_literal_kernel(const float *__restri
   }
 }
 
+// w . x in fp32, 8 values a step: the sum where the split one is not finite.
+// An infinite value times a zero part of a weight, or parts of opposite signs,
+// would make a NaN of what is an infinity.
+template <typename TS, typename Chunk>
+__device__ __forceinline__ float whole_dot(const float *__restrict__ w, int nch, const Chunk &chunk) {
+  float t = 0.0f;
+#pragma unroll 1
+  for (int ch = 0; ch < nch; ++ch) {
+    float v[8];
+    Elem<TS>::unpack(chunk(ch), v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t = fmaf(w[8 * ch + e], v[e], t);
+  }
+  return t;
+}
+
 // Rows of at most kTileMaxK values: a workgroup of four waves holds 16 RB
 // whole rows in LDS, so the layer has one barrier; wave w takes the feature
 // blocks w, w + 4, ..., its weights streaming from L2 four K steps ahead. Two
@@ -82,7 +98,8 @@ __global__ __launch_bounds__(256) void pack_literal_kernel(const float *__restri
 constexpr int kTileMaxK = 1024;
 
 template <typename TS, int RB, bool APPLY>
-__global__ __launch_bounds__(256) void se_literal_tile_kernel(TS *__restrict__ X, const TS *__restrict__ Wp,
+__global__ __launch_bounds__(256) void se_literal_tile_kernel(TS *__restrict__ X, const float *__restrict__ W,
+                                                              const TS *__restrict__ Wp,
                                                               const float *__restrict__ unscale,
                                                               const float *__restrict__ bias,
                                                               float *__restrict__ s, int64_t R, int32_t M,
@@ -155,7 +172,11 @@ __global__ __launch_bounds__(256) void se_literal_tile_kernel(TS *__restrict__ X
       for (int e = 0; e < 4; ++e) {
         const int n = fb * 16 + 4 * q + e;
         if (n < M) {
-          const float t = acc[j][e] * unscale[n] + bias[n];
+          float t = acc[j][e] * unscale[n] + bias[n];
+          if (!__builtin_isfinite(acc[j][e]))
+            t = whole_dot<TS>(W + (int64_t)n * K, nch, [&](int ch) {
+                  return *reinterpret_cast<const uint4 *>(at(16 * j + c, ch));
+                }) + bias[n];
           const float sv = 1.0f / (1.0f + expf(-t));
           if (r < R) s[r * M + n] = sv;
           if (APPLY) s_s[(16 * j + c) * ss + n] = sv;
@@ -188,7 +209,8 @@ __global__ __launch_bounds__(256) void se_literal_tile_kernel(TS *__restrict__ X
 // Longer rows: a wave takes 64 rows and 16 features straight from global
 // memory; the waves of a workgroup take the features of the same rows first.
 template <typename TS>
-__global__ __launch_bounds__(256) void se_literal_kernel(const TS *__restrict__ X, const TS *__restrict__ Wp,
+__global__ __launch_bounds__(256) void se_literal_kernel(const TS *__restrict__ X, const float *__restrict__ W,
+                                                         const TS *__restrict__ Wp,
                                                          const float *__restrict__ unscale,
                                                          const float *__restrict__ bias,
                                                          float *__restrict__ s, int64_t R, int32_t M,
@@ -246,7 +268,11 @@ __global__ __launch_bounds__(256) void se_literal_kernel(const TS *__restrict__ 
     for (int e = 0; e < 4; ++e) {
       const int n = fb * 16 + 4 * q + e;
       if (r < R && n < M) {
-        const float t = acc[j][e] * unscale[n] + bias[n];
+        float t = acc[j][e] * unscale[n] + bias[n];
+        if (!__builtin_isfinite(acc[j][e]))
+          t = whole_dot<TS>(W + (int64_t)n * K, nch, [&](int ch) {
+                return *reinterpret_cast<const uint4 *>(xp[j] + 8 * ch);
+              }) + bias[n];
         s[r * M + n] = 1.0f / (1.0f + expf(-t));
       }
     }
@@ -274,15 +300,15 @@ hipError_t launch_pack_literal(int dtype, const float *w, int32_t M, int32_t K, 
 }
 
 template <typename TS>
-static hipError_t se_literal_t(void *x, const void *wp, const float *unscale, const float *b, float *s_out,
+static hipError_t se_literal_t(void *x, const float *w, const void *wp, const float *unscale, const float *b, float *s_out,
                                int64_t R, int32_t M, int32_t K, int32_t d, bool apply, bool ll, hipStream_t s) {
   TS *X = static_cast<TS *>(x);
-  const TS *W = static_cast<const TS *>(wp);
+  const TS *Wp = static_cast<const TS *>(wp);
   if (K > kTileMaxK) {
     if (apply) return hipErrorInvalidValue;
     const int64_t n_waves = (R + 16 * kRB - 1) / (16 * kRB) * ((M + 15) / 16);
     if (n_waves > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(se_literal_kernel<TS>, dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, s, X, W,
+    hipLaunchKernelGGL(se_literal_kernel<TS>, dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, s, X, w, Wp,
                        unscale, b, s_out, R, M, K, n_waves);
     return hipGetLastError();
   }
@@ -294,25 +320,25 @@ static hipError_t se_literal_t(void *x, const void *wp, const float *unscale, co
   const int lcpg = __builtin_ctz(d / 8);
   const dim3 grid((unsigned)blocks);
   if (rb == 2 && apply)
-    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 2, true>), grid, dim3(256), shmem, s, X, W, unscale, b, s_out, R, M, K, lcpg, ll);
+    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 2, true>), grid, dim3(256), shmem, s, X, w, Wp, unscale, b, s_out, R, M, K, lcpg, ll);
   else if (rb == 2)
-    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 2, false>), grid, dim3(256), shmem, s, X, W, unscale, b, s_out, R, M, K, lcpg, ll);
+    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 2, false>), grid, dim3(256), shmem, s, X, w, Wp, unscale, b, s_out, R, M, K, lcpg, ll);
   else if (apply)
-    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 1, true>), grid, dim3(256), shmem, s, X, W, unscale, b, s_out, R, M, K, lcpg, ll);
+    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 1, true>), grid, dim3(256), shmem, s, X, w, Wp, unscale, b, s_out, R, M, K, lcpg, ll);
   else
-    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 1, false>), grid, dim3(256), shmem, s, X, W, unscale, b, s_out, R, M, K, lcpg, ll);
+    hipLaunchKernelGGL((se_literal_tile_kernel<TS, 1, false>), grid, dim3(256), shmem, s, X, w, Wp, unscale, b, s_out, R, M, K, lcpg, ll);
   return hipGetLastError();
 }
 
 bool se_literal_applies(int32_t K) { return K <= kTileMaxK; }
 
-hipError_t launch_se_literal(int dtype, void *x, const void *wp, const float *unscale, const float *b,
+hipError_t launch_se_literal(int dtype, void *x, const float *w, const void *wp, const float *unscale, const float *b,
                              float *s_out, int64_t R, int32_t M, int32_t K, int32_t d, bool apply, bool ll,
                              hipStream_t s) {
   if (R <= 0) return hipSuccess;
   if (K % 8 != 0 || d < 8 || (d & (d - 1)) != 0 || M * d != K) return hipErrorInvalidValue;
-  if (dtype == kBF16) return se_literal_t<__bf16>(x, wp, unscale, b, s_out, R, M, K, d, apply, ll, s);
-  if (dtype == kF16) return se_literal_t<_Float16>(x, wp, unscale, b, s_out, R, M, K, d, apply, ll, s);
+  if (dtype == kBF16) return se_literal_t<__bf16>(x, w, wp, unscale, b, s_out, R, M, K, d, apply, ll, s);
+  if (dtype == kF16) return se_literal_t<_Float16>(x, w, wp, unscale, b, s_out, R, M, K, d, apply, ll, s);
   return hipErrorInvalidValue;
 }
 

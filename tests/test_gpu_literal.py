@@ -54,3 +54,38 @@ def test_literal_split(kw, cand):
         np.abs(o["x"]).sum(axis=1)) * 2 * np.max(np.abs(params["se_w1"]))
     assert np.max(np.abs(g["s"][sample] - o["s"])) <= min(bound, 1e-5)
     compare_scores(cfg, g["scores"][sample], o["scores"], f"literal split {kw}")
+
+
+@pytest.mark.parametrize("n_cross", [5, 46])     # rows held in LDS; longer ones
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_literal_infinite_value(dtype, n_cross):
+    """An infinite embedding value saturates its rows' weights by the sign of
+    its column of W, also where a weight needs fewer than three parts, and
+    leaves the other rows as they are."""
+    cfg = synth.config("serving_bf16", vocab=50, se_form="literal", dtype=dtype, n_user=4, n_ad=16,
+                       n_cross=n_cross)
+    log(f"test_literal_infinite_value {dtype} D_in {cfg.d_in}")
+    tables, params, batch = problem(cfg, seed=83, cand=[70, 19], model_seed=cfg.seed)
+    params = dict(params)
+    w = params["se_w1"].copy()
+    col = cfg.n_user * cfg.emb_dim
+    w[:, col] = np.where(np.arange(cfg.n_groups) % 2, np.float32(-0.1), np.float32(0.5))
+    params["se_w1"] = w
+    scores = []
+    for inf in (False, True):
+        if inf:
+            tables = list(tables)
+            t = tables[cfg.n_user].copy()
+            t[7, 0] = 0x7F80 if dtype == "bf16" else np.inf
+            tables[cfg.n_user] = t
+        run = GpuScorer(cfg, [device_table_from_numpy(t, cfg.dtype, "cuda") for t in tables], params, "cuda")
+        try:
+            scores.append(run.score(batch, want_s=True))
+        finally:
+            run.close()
+    hit = batch["ad_ids"][0] == 7
+    assert hit.any() and not hit.all()
+    want = (w[:, col] > 0).astype(np.float32)
+    assert np.array_equal(scores[1]["s"][hit], np.broadcast_to(want, (hit.sum(), cfg.n_groups)))
+    for k in ("s", "scores"):
+        assert np.array_equal(scores[1][k][~hit], scores[0][k][~hit])

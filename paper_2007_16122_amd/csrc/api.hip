@@ -597,9 +597,8 @@ int score_launch(cold_model *m, const cold_batch *b, unsigned char *W, float *sc
     // reweighting in place or, in large batches without a mask, as the
     // network reads the rows
     float *sb = importance ? importance : reinterpret_cast<float *>(W + wl.sbuf);
-    g.z_out = nullptr;
     if ((e = marks.mark("gather_raw")) != hipSuccess) return hip_fail(m, e, "profile event");
-    if ((e = launch_gather_se(m->dtype, kSqueezeRaw, false, m->hashed, g, s)) != hipSuccess)
+    if ((e = launch_gather_se(m->dtype, kRowsOnly, false, m->hashed, g, s)) != hipSuccess)
       return hip_fail(m, e, "gather (raw) launch");
     weigh_later = net_rows && l0 == 0 && !topk && !x_out;
     const bool weighed = !weigh_later && !topk && se_literal_applies(m->D_in);   // by the SE layer's kernel

@@ -192,10 +192,11 @@ struct GatherArgs {
 // kApplyWeights: reweight with s_buf (groups outside `mask`, when given,
 // read nothing and get weight 0); kRawOut: the concatenated embedding in
 // fp32 to X, for an SE computed elsewhere
-// kSqueezeRaw: the squeeze to z_out [R][M] (when not null) and the gathered
-// rows, exact in the storage type, to X, for an SE of its own and
-// apply_weights (models without sequences)
-enum GatherMode { kFull = 0, kWeightsOnly = 1, kApplyWeights = 2, kRawOut = 3, kSqueezeRaw = 4 };
+// kSqueezeRaw: the squeeze to z_out [R][M] and the gathered rows, exact in the
+// storage type, to X, for an SE of its own and apply_weights (models without
+// sequences); kRowsOnly: the rows alone. (The squeeze as a run-time choice cost
+// the 200-group model's call 1.4 of 118 us.)
+enum GatherMode { kFull = 0, kWeightsOnly = 1, kApplyWeights = 2, kRawOut = 3, kSqueezeRaw = 4, kRowsOnly = 5 };
 
 // launchers (return hipError_t of the launch)
 bool user_pool_needed(int dtype, const GatherArgs &a);

@@ -374,11 +374,18 @@ __global__ __launch_bounds__(kGatherThreads, CPT <= 8 ? 4 : 2) void gather_se_ke
       advance(t, c);
     }
   }
-  if constexpr (MODE == kFull || MODE == kWeightsOnly || MODE == kSqueezeRaw) {
+  if constexpr (MODE == kRowsOnly) {
+    TS *X = static_cast<TS *>(a.X);
+    int t = tf, c = cf;
+    asm volatile("" : "+v"(t), "+v"(c));
+#pragma unroll
+    for (int j = 0; j < CPT; ++j, advance(t, c)) {
+      const int i = ln + 64 * j;
+      if (t < tv) *reinterpret_cast<uint4 *>(X + (r0 * CPR + i) * EPC) = raw[j];
+    }
+  } else if constexpr (MODE == kFull || MODE == kWeightsOnly || MODE == kSqueezeRaw) {
     int t = tf, c = cf;
     asm volatile("" : "+v"(t), "+v"(c));   // recomputed per phase, not kept live
-    const bool squeeze = MODE != kSqueezeRaw || a.z_out != nullptr;   // the same for every wave
-    if (squeeze)
 #pragma unroll
     for (int j = 0; j < CPT; ++j, advance(t, c)) {
       const int g = c >> lcpg, p = c & (CPG - 1);
@@ -402,7 +409,7 @@ __global__ __launch_bounds__(kGatherThreads, CPT <= 8 ? 4 : 2) void gather_se_ke
     if constexpr (MODE == kSqueezeRaw) {
       // the squeeze [R][M] and the gathered rows, exact in the storage type,
       // into the network input's place, for the separate SE and apply passes
-      if (a.z_out) for (int it = ln; it < Tw * M; it += 64) {
+      for (int it = ln; it < Tw * M; it += 64) {
         const int t = fast_div(it, a.mg_m), g = it - t * M;
         if (r0 + t < R) a.z_out[r0 * M + it] = z[t * Mp + g];
       }
@@ -1501,6 +1508,11 @@ static hipError_t gather_se_dt(int mode, bool ll, bool hashed, const GatherArgs 
   if (mode == kSqueezeRaw) {
     if (a.n_seq > 0) return hipErrorInvalidValue;   // pooled sums are not exact in TS
     return gather_se_t<TS, kSqueezeRaw, false>(hashed, a, s);
+  }
+  if (mode == kRowsOnly) {
+    // pooled sums are not exact in TS; fp32 models keep the rows with kRawOut
+    if constexpr (std::is_same<TS, float>::value) return hipErrorInvalidValue;
+    else return a.n_seq > 0 ? hipErrorInvalidValue : gather_se_t<TS, kRowsOnly, false>(hashed, a, s);
   }
   if (mode == kRawOut) return gather_se_t<TS, kRawOut, false>(hashed, a, s);
   if (mode == kApplyWeights)

@@ -75,6 +75,12 @@ def stage_work(cfg, batch, stage, compact=False):
         return "hbm", R * nax * (idb + d * es) + R * cfg.d_in * 4 + Q * nus * d * 4
     if stage == "se_dense":
         return "mfma_f32", 2.0 * R * cfg.d_in * m
+    if stage == "se_literal":   # exact rows read, SE weights written
+        return "hbm", R * cfg.d_in * es + R * m * 4
+    if stage == "net":          # every layer, but the compacted first one
+        w = cfg.widths
+        return "mfma", 2.0 * R * sum(a * b for a, b in zip(w[:-1], w[1:])) - (
+            2.0 * R * w[0] * w[1] if compact else 0.0)
     if stage == "dense_tail":     # the last separate layer and the fused tail
         w = cfg.widths
         return "mfma", 2.0 * R * (w[-5] * w[-4] + w[-4] * w[-3] + w[-3] * w[-2] + w[-2] * w[-1])
@@ -942,8 +948,12 @@ def summarize_parity(run_dir, command):
 def _stage_sources(stage):
     """Source files that define a stage's kernel (with the shared header)."""
     if stage.startswith("dense") or stage in ("tail", "head", "se_dense"):
-        return ("mlp.hip", "cold_internal.h")
-    return ("gather.hip", "cold_internal.h")
+        return ("mlp.hip", "mlp_tile.h", "cold_internal.h")
+    if stage == "net":
+        return ("net_rows.hip", "mlp_tile.h", "cold_internal.h")
+    if stage == "se_literal":
+        return ("se_literal.hip", "cold_internal.h")
+    return ("gather.hip", "gather_split.hip", "gather_tile.h", "cold_internal.h")
 
 
 def load_traffic(workload):
